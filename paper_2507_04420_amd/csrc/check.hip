@@ -19,73 +19,258 @@ using mmi::fail;
 
 namespace {
 
-template <typename OffT>
-__device__ __forceinline__ bool has_entry(const OffT* off, const int32_t* nbr, int64_t x, int64_t y) {
-  for (int64_t i = (int64_t)off[x]; i < (int64_t)off[x + 1]; ++i)
-    if (nbr[i] == y) return true;
-  return false;
+// Lists longer than this are checked by the whole wavefront, one after the
+// other; those up to it are laid end to end (scan_lists). It also bounds the
+// laid-out length of a wavefront's 64 lists, which then fits 32 bits.
+constexpr int64_t kFlatList = 2048;
+// A matched vertex whose list is longer than this leaves the search for its
+// edge to its mate when the mate's list is shorter.
+constexpr int64_t kOwnList = 32;
+constexpr int kThreads = 1024;
+constexpr int kWindow = 256;  // laid-out entries a wavefront takes per step, four a lane
+
+// One list to examine: for y >= 0, whether it holds y; else (x is unmatched)
+// how many of its entries lead to other unmatched vertices.
+struct List {
+  const int32_t* p;     // its first entry
+  const int32_t* mate;  // mates of the list's graph
+  int32_t n, x, y;
+  int32_t start;        // position of its first entry in the laid-out order
+};
+
+// One wavefront's LDS.
+struct WaveLds {
+  List list[64];
+  uint32_t head[kWindow / 4];  // byte p: a list starts at position p of the window
+  uint8_t found[64];
+};
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// LDS written by one lane is read by another lane of the same wavefront.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Examines one list per lane (len <= 0: none) with the whole wavefront.
+// Returns whether this lane's list holds its y; adds the uncovered entries of
+// the others to *uncovered.
+//
+// The lists are laid end to end and taken kWindow entries at a time: every
+// lane reads four ids, then the four mates those lead to, whatever the lists'
+// lengths, so that a long list does not hold the other 63 lanes and the loads
+// of a step are independent. The list an entry belongs to is the count of
+// list starts up to it: starts are marked in LDS and counted with a ballot.
+__device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLds& w,
+                                           unsigned long long* uncovered) {
+  const int lane = (int)(threadIdx.x & 63);
+  const bool flat = len > 0 && len <= kFlatList;
+  const uint64_t fm = __ballot(flat);
+  const uint64_t below_or_self = (2ull << lane) - 1;
+  bool hit = false;
+  if (fm) {
+    // inclusive prefix sum of the flat lists' lengths
+    int32_t sum = flat ? (int32_t)len : 0;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int32_t o = __shfl_up(sum, d, 64);
+      if (lane >= d) sum += o;
+    }
+    const int32_t total = __shfl(sum, 63, 64);
+    const int32_t start = sum - (flat ? (int32_t)len : 0);
+    const uint32_t slot = lanes_below(fm);
+    if (flat) {
+      List l = mine;
+      l.start = start;
+      w.list[slot] = l;
+      w.found[slot] = 0;
+    }
+    int32_t before = -1;  // lists started before the window, less one
+    for (int32_t base = 0; base < total; base += kWindow) {
+      w.head[lane] = 0;
+      wave_sync();
+      if (flat && start >= base && start < base + kWindow)
+        reinterpret_cast<uint8_t*>(w.head)[start - base] = 1;
+      wave_sync();
+      int32_t id[4];
+      int at[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint64_t h = __ballot(reinterpret_cast<const uint8_t*>(w.head)[q * 64 + lane] != 0);
+        at[q] = before + (int)__popcll(h & below_or_self);
+        before += (int)__popcll(h);
+        const int32_t pos = base + q * 64 + lane;
+        id[q] = pos < total ? w.list[at[q]].p[pos - w.list[at[q]].start] : -1;
+      }
+      wave_sync();
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (base + q * 64 + lane >= total) continue;
+        const List& l = w.list[at[q]];
+        if (l.y >= 0) {
+          if (id[q] == l.y) w.found[at[q]] = 1;
+        } else if (id[q] >= 0 && id[q] < l.n && id[q] != l.x) {
+          *uncovered += l.mate[id[q]] == -1;
+        }
+      }
+    }
+    wave_sync();
+    hit = flat && w.found[slot] != 0;
+    wave_sync();
+  }
+  uint64_t longs = __ballot(len > kFlatList);
+  while (longs) {
+    const int src = __builtin_ctzll(longs);
+    longs &= longs - 1;
+    const int32_t* p = reinterpret_cast<const int32_t*>(__shfl((long long)mine.p, src, 64));
+    const int32_t* mate = reinterpret_cast<const int32_t*>(__shfl((long long)mine.mate, src, 64));
+    const int64_t m = __shfl((long long)len, src, 64);
+    const int32_t n = __shfl(mine.n, src, 64), x = __shfl(mine.x, src, 64), y = __shfl(mine.y, src, 64);
+    bool any = false;
+    for (int64_t i = 0; i < m && !any; i += kWindow) {
+      int32_t id[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) id[q] = i + q * 64 + lane < m ? p[i + q * 64 + lane] : -1;
+      if (y >= 0) {
+        any = __ballot(id[0] == y || id[1] == y || id[2] == y || id[3] == y) != 0;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (id[q] >= 0 && id[q] < n && id[q] != x) *uncovered += mate[id[q]] == -1;
+      }
+    }
+    if (lane == src) hit = any;
+  }
+  return hit;
+}
+
+// Checks 64 vertices, one per lane (valid: the lane has one): vertex x of a
+// graph of n vertices whose offsets, ids and mates are based at its first
+// vertex.
+//
+// A pair's edge may be in either end's list. An end with a short list searches
+// its own, which is read coalesced with its neighbours in the block; an end
+// with a long list leaves the search to its mate if that has the shorter one
+// (the search of a hub's list for one id would read most of it), and the end
+// that searches counts for both. An edge not found there is searched in the
+// other list (one-sided input).
+template <typename OffT>
+__device__ __forceinline__ void check_vertices(const OffT* off, const int32_t* nbr, int64_t n,
+                                               const int32_t* mate, int64_t x, bool valid,
+                                               WaveLds& w, unsigned long long c[6]) {
+  List l{nullptr, mate, (int32_t)n, (int32_t)x, -1, 0};
+  int64_t len = 0;
+  unsigned weight = 1;
+  bool search = false;
+  if (valid) {
+    const int64_t y = mate[x];
+    const int64_t b = (int64_t)off[x], e = (int64_t)off[x + 1];
+    if (y < -1 || y >= n) {
+      ++c[0];
+    } else if (y == x) {
+      ++c[1];
+      ++c[5];
+    } else if (y >= 0) {
+      ++c[5];
+      const bool mutual = (int64_t)mate[y] == x;
+      if (!mutual) ++c[2];
+      search = true;
+      if (mutual && e - b > kOwnList) {
+        const int64_t ly = (int64_t)off[y + 1] - (int64_t)off[y];
+        if (ly <= kOwnList || ly < e - b || (ly == e - b && y < x))
+          search = false;
+        else
+          weight = 2;  // the mate's list is longer: it leaves the search to this end
+      }
+      l.y = (int32_t)y;
+    }
+    if (search || y == -1) {
+      l.p = nbr + b;
+      len = e - b;
+    }
+  }
+  bool hit = scan_lists(l, len, w, &c[4]);
+  const bool again = search && !hit;
+  if (!__ballot(again)) return;
+  len = 0;
+  if (again) {
+    const int64_t y = l.y, b = (int64_t)off[y], e = (int64_t)off[y + 1];
+    // a mate with a long list has left the search to this end
+    if (weight == 1 && e - b > kOwnList && (int64_t)mate[y] == x) weight = 2;
+    l.y = (int32_t)x;
+    l.p = nbr + b;
+    len = e - b;
+  }
+  hit = scan_lists(l, len, w, &c[4]);
+  if (again && !hit) c[3] += weight;
+}
+
+// Sums the block's counts and adds them to out, one atomic per nonzero count
+// and block: atomics of all blocks on the same six words are done one after
+// the other, about 12 ns each.
 __device__ __forceinline__ void flush_counts(unsigned long long c[6], unsigned long long* out) {
+  __shared__ unsigned long long part[kThreads / 64][6];
+  const int lane = (int)(threadIdx.x & 63);
 #pragma unroll
   for (int k = 0; k < 6; ++k) {
     unsigned long long s = c[k];
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
-    if ((threadIdx.x & 63) == 0 && s)
-      __hip_atomic_fetch_add(out + k, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) part[threadIdx.x >> 6][k] = s;
   }
-}
-
-// One vertex x of a graph whose arrays are based at its first vertex.
-template <typename OffT>
-__device__ __forceinline__ void check_vertex(const OffT* off, const int32_t* nbr, int64_t n,
-                                             const int32_t* mate, int64_t x,
-                                             unsigned long long c[6]) {
-  const int64_t y = mate[x];
-  if (y < -1 || y >= n) {
-    ++c[0];
-  } else if (y == x) {
-    ++c[1];
-    ++c[5];
-  } else if (y >= 0) {
-    ++c[5];
-    if ((int64_t)mate[y] != x) ++c[2];
-    if (!has_entry(off, nbr, x, y) && !has_entry(off, nbr, y, x)) ++c[3];
-  } else {
-    // x unmatched: every other endpoint of its entries must be matched
-    for (int64_t i = (int64_t)off[x]; i < (int64_t)off[x + 1]; ++i) {
-      const int64_t z = nbr[i];
-      if (z >= 0 && z < n && z != x && mate[z] == -1) ++c[4];
-    }
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    unsigned long long s = 0;
+    for (int q = 0; q < (int)(blockDim.x >> 6); ++q) s += part[q][threadIdx.x];
+    if (s)
+      __hip_atomic_fetch_add(out + threadIdx.x, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
 template <typename OffT>
-__global__ void check_kernel(const OffT* __restrict__ off, const int32_t* __restrict__ nbr,
-                             int64_t n, const int32_t* __restrict__ mate,
-                             unsigned long long* out) {
+__global__ __launch_bounds__(kThreads) void check_kernel(const OffT* __restrict__ off,
+                                                         const int32_t* __restrict__ nbr, int64_t n,
+                                                         const int32_t* __restrict__ mate,
+                                                         unsigned long long* out) {
+  __shared__ WaveLds lds[kThreads / 64];
   unsigned long long c[6] = {0, 0, 0, 0, 0, 0};
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n; x += stride)
-    check_vertex(off, nbr, n, mate, x, c);
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+       x - (int64_t)(threadIdx.x & 63) < n; x += stride)
+    check_vertices(off, nbr, n, mate, x, x < n, lds[threadIdx.x >> 6], c);
   flush_counts(c, out);
 }
 
-__global__ void check_batch_kernel(const mmb::GraphDesc* __restrict__ descs,
-                                   const int64_t* __restrict__ vtx_off, int32_t num_graphs,
-                                   const int32_t* __restrict__ mate, unsigned long long* out) {
+// The graph of global vertex v: the last one in [lo, hi) that starts at or
+// before it.
+__device__ __forceinline__ int graph_of(const int64_t* vtx_off, int lo, int hi, int64_t v) {
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (vtx_off[mid] <= v) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// A batch: 64 consecutive vertices lie in one graph unless it ends among them,
+// so the wavefront looks up its first vertex's graph once, and a lane past
+// that graph's end searches the graphs behind it.
+__global__ __launch_bounds__(kThreads) void check_batch_kernel(
+    const mmb::GraphDesc* __restrict__ descs, const int64_t* __restrict__ vtx_off,
+    int32_t num_graphs, const int32_t* __restrict__ mate, unsigned long long* out) {
+  __shared__ WaveLds lds[kThreads / 64];
   unsigned long long c[6] = {0, 0, 0, 0, 0, 0};
   const int64_t N = vtx_off[num_graphs];
+  const int lane = (int)(threadIdx.x & 63);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < N; v += stride) {
-    int lo = 0, hi = num_graphs;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (vtx_off[mid] <= v) lo = mid; else hi = mid;
-    }
-    const mmb::GraphDesc d = descs[lo];
-    check_vertex(d.off, d.nbr, d.n, mate + d.v0, v - d.v0, c);
+  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v - lane < N; v += stride) {
+    int g = graph_of(vtx_off, 0, num_graphs, v - lane);
+    if (v < N && v >= vtx_off[g + 1]) g = graph_of(vtx_off, g + 1, num_graphs, v);
+    const mmb::GraphDesc& d = descs[g];
+    check_vertices(d.off, d.nbr, d.n, mate + d.v0, v - d.v0, v < N, lds[threadIdx.x >> 6], c);
   }
   flush_counts(c, out);
 }
@@ -98,11 +283,17 @@ mm_status finish(unsigned long long* dev, hipStream_t s, int64_t* counts) {
   return MM_OK;
 }
 
-int blocks_for(int64_t n) {
-  int64_t b = (n + 255) / 256;
-  if (b < 1) b = 1;
-  if (b > 8192) b = 8192;
-  return (int)b;
+// At most 512 workgroups (two of 16 wavefronts fill a CU), so that few of them
+// add to the counts at the end; a graph too small for 512 large ones gets
+// smaller ones, down to a wavefront each, to be spread over all CUs.
+struct Grid {
+  unsigned blocks, threads;
+};
+Grid grid_of(int64_t n) {
+  int64_t t = 64;
+  while (t < kThreads && n > 512 * t) t *= 2;
+  const int64_t b = (n + t - 1) / t;
+  return Grid{(unsigned)(b > 512 ? 512 : b), (unsigned)t};
 }
 
 }  // namespace
@@ -117,12 +308,13 @@ mm_status mm_check(mm_handle h, void* stream, const int32_t* match, int64_t* cou
   HIP_TRY(hipMemsetAsync(dev, 0, 6 * sizeof(unsigned long long), s));
   const int64_t n = mmi::handle_n(h);
   if (n > 0) {
+    const Grid gr = grid_of(n);
     if (mmi::handle_off64(h))
-      hipLaunchKernelGGL((check_kernel<int64_t>), dim3(blocks_for(n)), dim3(256), 0, s,
+      hipLaunchKernelGGL((check_kernel<int64_t>), dim3(gr.blocks), dim3(gr.threads), 0, s,
                          static_cast<const int64_t*>(mmi::handle_off(h)), mmi::handle_nbr(h), n,
                          match, dev);
     else
-      hipLaunchKernelGGL((check_kernel<int32_t>), dim3(blocks_for(n)), dim3(256), 0, s,
+      hipLaunchKernelGGL((check_kernel<int32_t>), dim3(gr.blocks), dim3(gr.threads), 0, s,
                          static_cast<const int32_t*>(mmi::handle_off(h)), mmi::handle_nbr(h), n,
                          match, dev);
     HIP_TRY(hipGetLastError());
@@ -138,7 +330,8 @@ mm_status mm_batch_check(mm_batch_handle b, void* stream, const int32_t* match, 
   unsigned long long* dev = reinterpret_cast<unsigned long long*>(info.ws + mmi::kCheckOffset);
   HIP_TRY(hipMemsetAsync(dev, 0, 6 * sizeof(unsigned long long), s));
   if (info.N > 0) {
-    hipLaunchKernelGGL(check_batch_kernel, dim3(blocks_for(info.N)), dim3(256), 0, s, info.descs,
+    const Grid gr = grid_of(info.N);
+    hipLaunchKernelGGL(check_batch_kernel, dim3(gr.blocks), dim3(gr.threads), 0, s, info.descs,
                        info.vtx_off, info.G, match, dev);
     HIP_TRY(hipGetLastError());
   }
