@@ -461,7 +461,9 @@ void mm_batch_destroy(mm_batch_handle h);
  * themselves; [2] asymmetric mates (mate[mate[x]] != x); [3] mates that are
  * not an edge in either list; [4] entries (x, y), x != y, with both ends
  * unmatched; [5] vertices whose mate is in [0, n). A maximal matching has counts[0..4] == 0.
- * For a batch, ids are local to each graph.
+ * For a batch, ids are local to each graph. mm_check on a large dense graph
+ * (2^23 vertices, 8 entries each, or more) takes n / 8 bytes of device memory
+ * for the call, stream-ordered, and does without where there is none.
  */
 mm_status mm_check(mm_handle h, void* stream, const int32_t* match, int64_t* counts);
 mm_status mm_batch_check(mm_batch_handle h, void* stream, const int32_t* match, int64_t* counts);

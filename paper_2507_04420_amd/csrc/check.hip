@@ -26,14 +26,26 @@ constexpr int64_t kFlatList = 2048;
 // A matched vertex whose list is longer than this leaves the search for its
 // edge to its mate when the mate's list is shorter.
 constexpr int64_t kOwnList = 32;
+// Single graphs of at least kBitsFrom vertices and kBitsDegree entries per
+// vertex get a bit per vertex for the scans of unmatched vertices: on a skewed
+// graph a quarter of the vertices stay unmatched, and every entry of theirs is
+// a random access, to a line of a mate array far larger than the 4 MB of an
+// XCD's L2, or to a bit of an array that fits it. The bits cost a pass over the
+// mates and an allocation (15 to 25 us), so below 2^23 vertices or on sparse
+// graphs, whose scans are few or local, they do not pay: check_kernel and
+// bits together, without and with, R-MAT-25 920 and 616 us, R-MAT-24 460 and 373,
+// ER of 2^24 vertices and 8 entries each 405 and 394; but ER of 2^22 and 16
+// 138 and 151, a mesh of 1e7 115 and 140.
+constexpr int64_t kBitsFrom = (int64_t)1 << 23;
+constexpr int64_t kBitsDegree = 8;
 constexpr int kThreads = 1024;
 constexpr int kWindow = 256;  // laid-out entries a wavefront takes per step, four a lane
 
 // One list to examine: for y >= 0, whether it holds y; else (x is unmatched)
 // how many of its entries lead to other unmatched vertices.
 struct List {
-  const int32_t* p;     // its first entry
-  const int32_t* mate;  // mates of the list's graph
+  const int32_t* p;  // its first entry
+  const void* free;  // the list's graph: its mates, or (BITS) a bit per vertex, set if unmatched
   int32_t n, x, y;
   int32_t start;        // position of its first entry in the laid-out order
 };
@@ -48,6 +60,12 @@ struct WaveLds {
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+template <bool BITS>
+__device__ __forceinline__ bool unmatched(const void* free, int32_t v) {
+  if (BITS) return (static_cast<const uint32_t*>(free)[v >> 5] >> (v & 31)) & 1u;
+  return static_cast<const int32_t*>(free)[v] == -1;
 }
 
 // LDS written by one lane is read by another lane of the same wavefront.
@@ -65,6 +83,7 @@ __device__ __forceinline__ void wave_sync() {
 // lengths, so that a long list does not hold the other 63 lanes and the loads
 // of a step are independent. The list an entry belongs to is the count of
 // list starts up to it: starts are marked in LDS and counted with a ballot.
+template <bool BITS>
 __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLds& w,
                                            unsigned long long* uncovered) {
   const int lane = (int)(threadIdx.x & 63);
@@ -114,7 +133,7 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
         if (l.y >= 0) {
           if (id[q] == l.y) w.found[at[q]] = 1;
         } else if (id[q] >= 0 && id[q] < l.n && id[q] != l.x) {
-          *uncovered += l.mate[id[q]] == -1;
+          *uncovered += unmatched<BITS>(l.free, id[q]);
         }
       }
     }
@@ -127,7 +146,7 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
     const int src = __builtin_ctzll(longs);
     longs &= longs - 1;
     const int32_t* p = reinterpret_cast<const int32_t*>(__shfl((long long)mine.p, src, 64));
-    const int32_t* mate = reinterpret_cast<const int32_t*>(__shfl((long long)mine.mate, src, 64));
+    const void* free = reinterpret_cast<const void*>(__shfl((long long)mine.free, src, 64));
     const int64_t m = __shfl((long long)len, src, 64);
     const int32_t n = __shfl(mine.n, src, 64), x = __shfl(mine.x, src, 64), y = __shfl(mine.y, src, 64);
     bool any = false;
@@ -140,7 +159,7 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
       } else {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-          if (id[q] >= 0 && id[q] < n && id[q] != x) *uncovered += mate[id[q]] == -1;
+          if (id[q] >= 0 && id[q] < n && id[q] != x) *uncovered += unmatched<BITS>(free, id[q]);
       }
     }
     if (lane == src) hit = any;
@@ -150,7 +169,11 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
 
 // Checks 64 vertices, one per lane (valid: the lane has one): vertex x of a
 // graph of n vertices whose offsets, ids and mates are based at its first
-// vertex.
+// vertex; free: the mates again, or (BITS) its bits of unmatched vertices.
+//
+// mate[mate[x]] == x is read (a random access) by the lower end only: counting
+// every matched vertex as asymmetric and taking two off for each mutual pair
+// leaves the vertices whose mate does not name them.
 //
 // A pair's edge may be in either end's list. An end with a short list searches
 // its own, which is read coalesced with its neighbours in the block; an end
@@ -158,11 +181,11 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
 // (the search of a hub's list for one id would read most of it), and the end
 // that searches counts for both. An edge not found there is searched in the
 // other list (one-sided input).
-template <typename OffT>
+template <typename OffT, bool BITS>
 __device__ __forceinline__ void check_vertices(const OffT* off, const int32_t* nbr, int64_t n,
-                                               const int32_t* mate, int64_t x, bool valid,
-                                               WaveLds& w, unsigned long long c[6]) {
-  List l{nullptr, mate, (int32_t)n, (int32_t)x, -1, 0};
+                                               const int32_t* mate, const void* free, int64_t x,
+                                               bool valid, WaveLds& w, unsigned long long c[6]) {
+  List l{nullptr, free, (int32_t)n, (int32_t)x, -1, 0};
   int64_t len = 0;
   unsigned weight = 1;
   bool search = false;
@@ -176,10 +199,12 @@ __device__ __forceinline__ void check_vertices(const OffT* off, const int32_t* n
       ++c[5];
     } else if (y >= 0) {
       ++c[5];
-      const bool mutual = (int64_t)mate[y] == x;
-      if (!mutual) ++c[2];
+      ++c[2];
+      const bool longl = e - b > kOwnList;
+      const bool mutual = (x < y || longl) && (int64_t)mate[y] == x;
+      if (mutual && x < y) c[2] -= 2;
       search = true;
-      if (mutual && e - b > kOwnList) {
+      if (mutual && longl) {
         const int64_t ly = (int64_t)off[y + 1] - (int64_t)off[y];
         if (ly <= kOwnList || ly < e - b || (ly == e - b && y < x))
           search = false;
@@ -193,7 +218,7 @@ __device__ __forceinline__ void check_vertices(const OffT* off, const int32_t* n
       len = e - b;
     }
   }
-  bool hit = scan_lists(l, len, w, &c[4]);
+  bool hit = scan_lists<BITS>(l, len, w, &c[4]);
   const bool again = search && !hit;
   if (!__ballot(again)) return;
   len = 0;
@@ -205,7 +230,7 @@ __device__ __forceinline__ void check_vertices(const OffT* off, const int32_t* n
     l.p = nbr + b;
     len = e - b;
   }
-  hit = scan_lists(l, len, w, &c[4]);
+  hit = scan_lists<BITS>(l, len, w, &c[4]);
   if (again && !hit) c[3] += weight;
 }
 
@@ -231,17 +256,29 @@ __device__ __forceinline__ void flush_counts(unsigned long long c[6], unsigned l
   }
 }
 
-template <typename OffT>
+// One bit per vertex, set if it is unmatched.
+__global__ void free_bits_kernel(const int32_t* __restrict__ mate, int64_t n,
+                                 uint64_t* __restrict__ bits) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int lane = (int)(threadIdx.x & 63);
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x - lane < n; x += stride) {
+    const uint64_t m = __ballot(x < n && mate[x] == -1);
+    if (lane == 0) bits[x >> 6] = m;
+  }
+}
+
+template <typename OffT, bool BITS>
 __global__ __launch_bounds__(kThreads) void check_kernel(const OffT* __restrict__ off,
                                                          const int32_t* __restrict__ nbr, int64_t n,
                                                          const int32_t* __restrict__ mate,
+                                                         const void* __restrict__ free,
                                                          unsigned long long* out) {
   __shared__ WaveLds lds[kThreads / 64];
   unsigned long long c[6] = {0, 0, 0, 0, 0, 0};
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
        x - (int64_t)(threadIdx.x & 63) < n; x += stride)
-    check_vertices(off, nbr, n, mate, x, x < n, lds[threadIdx.x >> 6], c);
+    check_vertices<OffT, BITS>(off, nbr, n, mate, free, x, x < n, lds[threadIdx.x >> 6], c);
   flush_counts(c, out);
 }
 
@@ -267,10 +304,14 @@ __global__ __launch_bounds__(kThreads) void check_batch_kernel(
   const int lane = (int)(threadIdx.x & 63);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v - lane < N; v += stride) {
-    int g = graph_of(vtx_off, 0, num_graphs, v - lane);
+    // wavefront-uniform: the search runs in scalar registers
+    const int64_t first = ((int64_t)__builtin_amdgcn_readfirstlane((int)((v - lane) >> 32)) << 32) |
+                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(v - lane));
+    int g = graph_of(vtx_off, 0, num_graphs, first);
     if (v < N && v >= vtx_off[g + 1]) g = graph_of(vtx_off, g + 1, num_graphs, v);
     const mmb::GraphDesc& d = descs[g];
-    check_vertices(d.off, d.nbr, d.n, mate + d.v0, v - d.v0, v < N, lds[threadIdx.x >> 6], c);
+    const int32_t* m = mate + d.v0;
+    check_vertices<int64_t, false>(d.off, d.nbr, d.n, m, m, v - d.v0, v < N, lds[threadIdx.x >> 6], c);
   }
   flush_counts(c, out);
 }
@@ -296,6 +337,17 @@ Grid grid_of(int64_t n) {
   return Grid{(unsigned)(b > 512 ? 512 : b), (unsigned)t};
 }
 
+template <typename OffT>
+void launch_check(const Grid& gr, const OffT* off, const int32_t* nbr, int64_t n, const int32_t* mate,
+                  const uint64_t* bits, unsigned long long* dev, hipStream_t s) {
+  if (bits)
+    hipLaunchKernelGGL((check_kernel<OffT, true>), dim3(gr.blocks), dim3(gr.threads), 0, s, off, nbr,
+                       n, mate, bits, dev);
+  else
+    hipLaunchKernelGGL((check_kernel<OffT, false>), dim3(gr.blocks), dim3(gr.threads), 0, s, off, nbr,
+                       n, mate, mate, dev);
+}
+
 }  // namespace
 
 extern "C" {
@@ -309,15 +361,23 @@ mm_status mm_check(mm_handle h, void* stream, const int32_t* match, int64_t* cou
   const int64_t n = mmi::handle_n(h);
   if (n > 0) {
     const Grid gr = grid_of(n);
+    uint64_t* bits = nullptr;
+    if (n >= kBitsFrom && mmi::handle_m(h) / n >= kBitsDegree &&
+        hipMallocAsync(reinterpret_cast<void**>(&bits), (size_t)((n + 63) / 64) * 8, s) != hipSuccess) {
+      bits = nullptr;  // no memory for them: the mates themselves are read
+      (void)hipGetLastError();
+    }
+    if (bits)
+      hipLaunchKernelGGL(free_bits_kernel, dim3(2048), dim3(256), 0, s, match, n, bits);
     if (mmi::handle_off64(h))
-      hipLaunchKernelGGL((check_kernel<int64_t>), dim3(gr.blocks), dim3(gr.threads), 0, s,
-                         static_cast<const int64_t*>(mmi::handle_off(h)), mmi::handle_nbr(h), n,
-                         match, dev);
+      launch_check(gr, static_cast<const int64_t*>(mmi::handle_off(h)), mmi::handle_nbr(h), n, match,
+                   bits, dev, s);
     else
-      hipLaunchKernelGGL((check_kernel<int32_t>), dim3(gr.blocks), dim3(gr.threads), 0, s,
-                         static_cast<const int32_t*>(mmi::handle_off(h)), mmi::handle_nbr(h), n,
-                         match, dev);
-    HIP_TRY(hipGetLastError());
+      launch_check(gr, static_cast<const int32_t*>(mmi::handle_off(h)), mmi::handle_nbr(h), n, match,
+                   bits, dev, s);
+    const hipError_t e = hipGetLastError();
+    if (bits) (void)hipFreeAsync(bits, s);
+    HIP_TRY(e);
   }
   return finish(dev, s, counts);
 }

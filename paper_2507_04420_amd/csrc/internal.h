@@ -32,6 +32,7 @@ size_t hint_bytes(int64_t n, const mm_tuning& t);
 
 // Accessors of a single-graph handle (defined with the handle).
 int64_t handle_n(const mm_graph* h);
+int64_t handle_m(const mm_graph* h);
 int handle_off64(const mm_graph* h);
 const void* handle_off(const mm_graph* h);
 const int32_t* handle_nbr(const mm_graph* h);

@@ -377,6 +377,7 @@ struct mm_graph {
 
 namespace mmi {
 int64_t handle_n(const mm_graph* h) { return h->n; }
+int64_t handle_m(const mm_graph* h) { return h->m; }
 int handle_off64(const mm_graph* h) { return h->off64; }
 const void* handle_off(const mm_graph* h) { return h->off; }
 const int32_t* handle_nbr(const mm_graph* h) { return h->nbr; }

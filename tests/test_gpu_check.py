@@ -135,3 +135,70 @@ def test_probe_ceilings_are_plausible():
     r, a = ctypes.c_double(), ctypes.c_double()
     assert lib.mm_probe_ceilings(1 << 28, 1 << 24, None, ctypes.byref(r), ctypes.byref(a)) == 0
     assert 1e9 < r.value < 1e12 and 1e8 < a.value < 1e12, (r.value, a.value)
+
+
+def two_hubs(k, one_sided):
+    """Hubs 0 and 1 joined to each other and to k leaves each; an unmatched
+    vertex k + k + 2 with a list as long, of vertices all matched or not."""
+    leaves = np.arange(2, 2 + 2 * k)
+    e = [(0, 1)] + [(0, int(v)) for v in leaves[:k]] + [(1, int(v)) for v in leaves[k:]]
+    e += [(2 * k + 2, int(v)) for v in leaves]
+    return graphgen.from_edges(2 * k + 3, e, symmetric=not one_sided)
+
+
+# lists at the lengths where the check changes its way: searched by its own end
+# (32), laid end to end (2048), read by the whole wavefront; windows of 256
+@pytest.mark.parametrize("k", [1, 30, 31, 32, 255, 256, 1024, 2046, 2047, 2048, 5000])
+@pytest.mark.parametrize("one_sided", [False, True])
+def test_check_long_lists(k, one_sided):
+    csr = two_hubs(k, one_sided)
+    g = mm.Graph(torch.from_numpy(csr.off).cuda(), torch.from_numpy(csr.nbr).cuda())
+    n = csr.n
+    for case in range(6):
+        mate = np.full(n, -1, dtype=np.int32)
+        if case != 1:
+            mate[0], mate[1] = 1, 0  # an edge, the first entry of one list
+        if case == 2:  # not an edge: a leaf of one hub with a leaf of the other
+            mate[2], mate[n - 2] = n - 2, 2
+        elif case == 3:  # the last entry of a hub's list, named by one end only
+            mate[0], mate[1 + k] = 1 + k, 0
+        elif case == 4:  # a hub with no list in common
+            mate[0], mate[n - 1] = n - 1, 0
+        elif case == 5:  # the long-listed vertex matched, everything else free
+            mate[:] = -1
+            mate[n - 1], mate[2] = 2, n - 1
+        compare(g.check(torch.from_numpy(mate).cuda()), oracle.check(csr, mate))
+    g.close()
+
+
+# the smallest graph that gets a bit per vertex, and one vertex less
+@pytest.mark.parametrize("n", [(1 << 23) - 1, (1 << 23) + 37])
+def test_check_large_dense(n):
+    csr = graphgen.er(n, 8.2, seed=2)
+    assert csr.m >= 8 * n
+    g = mm.Graph(torch.from_numpy(csr.off).cuda(), torch.from_numpy(csr.nbr).cuda(), symmetric=True)
+    rng = np.random.default_rng(n)
+    for kind in ("none", "mixed"):
+        mate = corrupt(csr, oracle.sgmm(csr).mate, kind, rng, k=1000)
+        compare(g.check(torch.from_numpy(mate).cuda()), oracle.check(csr, mate))
+    g.close()
+
+
+# graphs that end inside a wavefront's 64 vertices, empty ones among them
+def test_batch_check_ragged_members():
+    sizes = [1, 63, 64, 65, 2, 1, 1, 130, 1000, 1, 127]
+    parts = [graphgen.er(max(s, 2), 4.0, seed=s) for s in sizes]
+    off, nbr, vtx = [0], [], [0]
+    for p in parts:
+        vtx += [vtx[-1], vtx[-1] + p.n]  # an empty graph before each
+        off += (p.off[1:] + off[-1]).tolist()
+        nbr.append(p.nbr)
+    off = np.array(off, dtype=np.int64)
+    b = mm.Batch(torch.from_numpy(off).cuda(), torch.from_numpy(np.concatenate(nbr)).cuda(), vtx, symmetric=True)
+    rng = np.random.default_rng(5)
+    mates = [corrupt(p, oracle.sgmm(p).mate, "range" if p.n > 10 else "none", rng, k=3) for p in parts]
+    got = b.check(torch.from_numpy(np.concatenate(mates)).cuda())
+    want = [oracle.check(p, mt) for p, mt in zip(parts, mates)]
+    for gf, wf in FIELDS:
+        assert got[gf] == sum(getattr(w, wf) for w in want), (gf, got, want)
+    b.close()
