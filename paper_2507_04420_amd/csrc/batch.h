@@ -60,8 +60,7 @@ struct BatchPlan {
   // their own before the persistent sweep
   const WorkItem* lds_items;
   int64_t n_lds;
-  int32_t lds_words;  // LDS words per wavefront (0: no such graph)
-  int lds_wg;         // threads per workgroup of that kernel
+  int32_t lds_words;  // LDS words of the largest of them (0: no such graph)
 };
 
 // Enqueues one pass: fills, queue reset, persistent sweep, output fix-up.

@@ -189,25 +189,21 @@ __global__ __launch_bounds__(256) void batch_sweep_kernel(SweepParams p,
   if (STATS) cnt.flush(stats);
 }
 
-// Graphs flagged kWholeLds, one wavefront each, their states in LDS
-// (whole.h): lds_words words of the dynamic LDS per wavefront. A kernel of its
-// own, so that the persistent sweep keeps its register budget.
+// Graphs flagged kWholeLds, one wavefront and workgroup each, their states in
+// LDS (whole.h). A kernel of its own, so that the persistent sweep keeps its
+// register budget; a workgroup per graph, so that a graph's LDS is free for
+// another as soon as it is done, not with the slowest of four.
 template <bool STATS>
-__global__ __launch_bounds__(256) void batch_whole_lds_kernel(SweepParams p,
-                                                             const GraphDesc* __restrict__ descs,
-                                                             const WorkItem* __restrict__ items,
-                                                             int64_t n_items, int32_t* mate,
-                                                             unsigned long long* stats,
-                                                             int32_t lds_words) {
-  __shared__ QSlot queues[4][kQueue];
+__global__ __launch_bounds__(64) void batch_whole_lds_kernel(SweepParams p,
+                                                            const GraphDesc* __restrict__ descs,
+                                                            const WorkItem* __restrict__ items,
+                                                            int32_t* mate,
+                                                            unsigned long long* stats) {
+  __shared__ QSlot queue[kQueue];
   extern __shared__ uint32_t whole_st[];
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (wave >= n_items) return;
   Counters<STATS> cnt;
-  const GraphDesc d = descs[items[wave].desc];
-  sweep_whole_lds<int64_t, STATS>(p, d.off, d.nbr, d.n, mate + d.v0,
-                                  whole_st + (int64_t)(threadIdx.x >> 6) * lds_words,
-                                  queues[threadIdx.x >> 6], cnt);
+  const GraphDesc d = descs[items[blockIdx.x].desc];
+  sweep_whole_lds<int64_t, STATS>(p, d.off, d.nbr, d.n, mate + d.v0, whole_st, queue, cnt);
   if (STATS) cnt.flush(stats);
 }
 
@@ -256,12 +252,9 @@ void fill(uint32_t* p, int64_t words, uint32_t v, hipStream_t s) {
 template <bool STATS>
 hipError_t launch_whole_lds(const BatchPlan& bp, hipStream_t s) {
   if (bp.n_lds == 0) return hipSuccess;
-  const int wpb = bp.lds_wg / 64;
-  const size_t shmem = (size_t)wpb * (size_t)bp.lds_words * 4;
-  const int64_t blocks = (bp.n_lds + wpb - 1) / wpb;
-  hipLaunchKernelGGL((batch_whole_lds_kernel<STATS>), dim3((unsigned)blocks), dim3(bp.lds_wg),
-                     shmem, s, bp.params, bp.descs, bp.lds_items, bp.n_lds, bp.mate, bp.stats,
-                     bp.lds_words);
+  hipLaunchKernelGGL((batch_whole_lds_kernel<STATS>), dim3((unsigned)bp.n_lds), dim3(64),
+                     (size_t)bp.lds_words * 4, s, bp.params, bp.descs, bp.lds_items, bp.mate,
+                     bp.stats);
   return hipGetLastError();
 }
 
@@ -579,6 +572,9 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
       return fail(MM_ERR_HIP, "building the hub table failed: %s", hipGetErrorString(e));
     }
   }
+  // the graphs kept in LDS, largest first: the last to start are the shortest
+  std::stable_sort(lds_items.begin(), lds_items.end(),
+                   [](const mmb::WorkItem& a, const mmb::WorkItem& b) { return a.nv > b.nv; });
   const int64_t n_main = (int64_t)items.size();
   items.insert(items.end(), lds_items.begin(), lds_items.end());
   if (!items.empty()) {
@@ -658,16 +654,10 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
   p.st_words = lay.st_words;
   p.hint_base = hint_base;
   p.lds_words = (int32_t)((lds_words + 3) / 4 * 4);  // 16-byte aligned regions
-  p.lds_wg = t.wg_size;
   if (p.lds_words > 0) {
-    // fewer wavefronts per workgroup if their LDS regions and the queues do
-    // not fit one workgroup's LDS (results do not depend on the group size)
     int max_lds = 0;
     HIP_TRY(hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-    const int64_t fixed = (int64_t)sizeof(mmk::QSlot) * mmk::kQueue * 4;
-    p.lds_wg = t.wg_size;
-    while (p.lds_wg > 64 && fixed + (int64_t)(p.lds_wg / 64) * p.lds_words * 4 > max_lds)
-      p.lds_wg -= 64;
+    const int64_t fixed = (int64_t)sizeof(mmk::QSlot) * mmk::kQueue;
     if (fixed + (int64_t)p.lds_words * 4 > max_lds) {
       mm_batch_destroy(b);
       return fail(MM_ERR_UNSUPPORTED, "LDS per workgroup (%d bytes) too small for whole-graph "

@@ -156,7 +156,7 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int l) {
 }
 
 // One queued source of a wavefront's front end (kept in LDS).
-struct QSlot {
+struct alignas(16) QSlot {
   int64_t b, e;
   int32_t x;
   uint32_t word;  // the filter word read for x (a first guess for a CAS on x)
