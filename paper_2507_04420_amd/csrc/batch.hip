@@ -151,7 +151,8 @@ __global__ __launch_bounds__(256) void batch_sweep_kernel(SweepParams p,
                                                          int64_t n_items, int32_t* mate,
                                                          uint32_t* queue,
                                                          unsigned long long* stats) {
-  __shared__ QSlot queues[4][kQueue];
+  extern __shared__ uint4 sweep_lds[];
+  QSlot* ring = wave_ring(sweep_lds, true);
   Counters<STATS> cnt;
   const int lane = (int)(threadIdx.x & 63);
   while (true) {
@@ -183,8 +184,8 @@ __global__ __launch_bounds__(256) void batch_sweep_kernel(SweepParams p,
         pp.disperse = 1;
       }
     }
-    sweep_block<int64_t, Layout, HINT, LAZY, STATS>(pp, d.off, d.nbr, L, w.vb, nv,
-                                                    queues[threadIdx.x >> 6], cnt);
+    sweep_block<int64_t, Layout, HINT, LAZY, STATS>(pp, d.off, d.nbr, L, w.vb, nv, ring,
+                                                    wave_noted(ring, noted_sources(pp.disperse)), cnt);
   }
   if (STATS) cnt.flush(stats);
 }
@@ -218,7 +219,8 @@ template <class Layout, bool HINT, bool LAZY, bool STATS>
 hipError_t launch_persistent(const BatchPlan& bp, hipStream_t s) {
   auto kern = batch_sweep_kernel<Layout, HINT, LAZY, STATS>;
   int per_cu = 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, bp.wg_size, 0);
+  const size_t lds = (bp.wg_size / 64) * wave_lds_bytes(true);  // meshes among the graphs
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, bp.wg_size, lds);
   if (e != hipSuccess) return e;
   if (per_cu < 1) per_cu = 1;
   const int wpb = bp.wg_size / 64;
@@ -226,7 +228,7 @@ hipError_t launch_persistent(const BatchPlan& bp, hipStream_t s) {
   const int64_t need = (bp.n_items + wpb - 1) / wpb;
   if (blocks > need) blocks = need;
   if (blocks < 1) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(bp.wg_size), 0, s, bp.params, bp.descs,
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(bp.wg_size), lds, s, bp.params, bp.descs,
                      bp.items, bp.n_items, bp.mate, bp.queue, bp.stats);
   return hipGetLastError();
 }

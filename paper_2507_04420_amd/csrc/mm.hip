@@ -236,7 +236,8 @@ __device__ __forceinline__ void sweep_graph(SweepParams p, const OffT* __restric
     if (threadIdx.x < 4) seen[threadIdx.x] = -1;
     __syncthreads();
   }
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const int64_t wave = uniform64(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const bool noted = noted_sources(p.disperse);
   int64_t vb, nv;
   if (wave < main_waves) {
     vb = v_begin + wave * p.wave_vertices;
@@ -265,9 +266,10 @@ __device__ __forceinline__ void sweep_graph(SweepParams p, const OffT* __restric
       return;
     }
   }
-  __shared__ QSlot queues[4][kQueue];  // one ring per wavefront (wg_size <= 256)
+  extern __shared__ uint4 sweep_lds[];
+  QSlot* ring = wave_ring(sweep_lds, noted);
   Counters<STATS> cnt;
-  sweep_block<OffT, Layout, HINT, LAZY, STATS>(p, off, nbr, L, vb, nv, queues[threadIdx.x >> 6],
+  sweep_block<OffT, Layout, HINT, LAZY, STATS>(p, off, nbr, L, vb, nv, ring, wave_noted(ring, noted),
                                                cnt);
   if (STATS) cnt.flush(stats);
 }
@@ -469,6 +471,7 @@ hipError_t launch_sweep(const mm_graph* g, const Layout& L, hipStream_t s) {
   pl.chunks = g->chunks;
   const int wpb = g->tun.wg_size / 64;
   const int64_t blocks = (waves + chunk_waves + wpb - 1) / wpb;
+  const size_t lds = wpb * wave_lds_bytes(noted_sources(p.disperse));
   if (blocks == 0) return hipSuccess;
   if (g->timing) {
     hipError_t e = hipEventRecord(g->timing->before(), s);
@@ -480,7 +483,7 @@ hipError_t launch_sweep(const mm_graph* g, const Layout& L, hipStream_t s) {
   if constexpr (!Layout::kRelabelled && !STATS) {
     if (g->tun.occupancy == 6) kernel = sweep_kernel_w6<OffT, Layout, HINT, LAZY, STATS>;
   }
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(g->tun.wg_size), 0, s, pl, off, nbr, g->n,
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(g->tun.wg_size), lds, s, pl, off, nbr, g->n,
                      v_begin, waves, g->n_chunks, g->chunk_count, L, stats);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
