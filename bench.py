@@ -969,8 +969,7 @@ def main():
         "config": cfg,
         "roofline": {
             "bound": "hbm",
-            # the six-wave build with occupancy = 6 (the same code)
-            "kernel": "sweep_kernel_w6" if cfg["tuning"].get("occupancy") == 6 else "sweep_kernel",
+            "kernel": "sweep_kernel",
             "achieved": round(achieved, 2),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",

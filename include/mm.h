@@ -179,8 +179,9 @@ typedef struct {
                             multiple of 64), its lanes taking sources
                             block/64 apart, so that lanes do not hold
                             neighbouring vertices; create measures the degrees
-                            on the device. 0: such graphs are cut like the
-                            others. Single graphs take their launch shape from
+                            on the device. min_waves shortens these blocks
+                            only as far as 32 would. 0: such graphs are cut
+                            like the others. Single graphs take their launch shape from
                             the tuning alone */
   int32_t wait_release;  /* 1: a lane that finds v reserved by another lane
                             releases u while it waits, and takes u again once
@@ -241,12 +242,10 @@ typedef struct {
                             2: every state read takes one candidate (ids are
                             still read scan_width at a time). 0: every read
                             takes a whole step's candidates */
-  int32_t occupancy;     /* 6: single-graph sweeps (not relabelled, not
-                            instrumented) run a build of the sweep kernel limited
-                            to 80 VGPRs, so that six wavefronts share each SIMD
-                            instead of five: more latency hidden, and more of the
-                            graph in flight at once. 0: the compiler's register
-                            budget. Batches ignore it */
+  int32_t occupancy;     /* 0 or 6: no effect (kept for stored tunings). 6 chose a
+                            build of the sweep kernel limited to six wavefronts'
+                            share of a SIMD's registers; every build now fits
+                            seven */
   int64_t iter_cap;      /* loop-trip budget per wavefront; 0 = default of
                             65536 + 8 x (neighbour entries of its block);
                             exceeding it raises MM_ERR_NO_PROGRESS */

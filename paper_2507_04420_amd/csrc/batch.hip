@@ -339,6 +339,8 @@ struct BatchLayout {  // byte offsets of the workspace pieces after the control 
   int64_t wave_vertices, mesh_wave_vertices;  // block lengths (shortened for a small batch)
 };
 
+constexpr int32_t kMeshMinWaves = 32;
+
 bool plan_layout(int32_t G, const int64_t* vtx_off, const mm_tuning& t, BatchLayout* out) {
   int64_t n_items = 0, st_words = 0, hint_words = 0;
   // sources swept in blocks (graphs not swept whole): too few of them for
@@ -350,8 +352,14 @@ bool plan_layout(int32_t G, const int64_t* vtx_off, const mm_tuning& t, BatchLay
     if (n > t.whole_graph_vertices) blocked += n;
   }
   const int64_t wv_main = mmi::short_blocks(blocked, t.wave_vertices, t.min_waves);
+  // a mesh's lanes take sources block / 64 apart, and the closer they are the
+  // longer the chains of lanes that wait for each other (16 graphs of the
+  // mixture: 152 us with blocks of 192, 497 with blocks of 64): its blocks are
+  // shortened only for a batch of too few sources for a few wavefronts
   const int64_t wv_mesh =
-      t.mesh_wave_vertices > 0 ? mmi::short_blocks(blocked, t.mesh_wave_vertices, t.min_waves) : 0;
+      t.mesh_wave_vertices > 0
+          ? mmi::short_blocks(blocked, t.mesh_wave_vertices, std::min(t.min_waves, kMeshMinWaves))
+          : 0;
   for (int32_t g = 0; g < G; ++g) {
     const int64_t n = vtx_off[g + 1] - vtx_off[g];
     // mesh graphs may take shorter blocks: room for the shorter of the two
@@ -470,6 +478,14 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
   auto* items_dev = reinterpret_cast<mmb::WorkItem*>(ws + lay.items);
   auto* vtx_dev = reinterpret_cast<int64_t*>(ws + lay.vtx);
   uint32_t* f = reinterpret_cast<uint32_t*>(ws);
+  // the host vectors are released on return: no upload may still read them
+  struct Uploads {
+    hipStream_t s;
+    bool waited = false;
+    ~Uploads() {
+      if (!waited) (void)hipStreamSynchronize(s);
+    }
+  } uploads{s};
   HIP_TRY(hipMemsetAsync(ws, 0, kCtrlBytes, s));
   if (G > 0)
     HIP_TRY(hipMemcpyAsync(descs_dev, descs.data(), sizeof(mmb::GraphDesc) * G,
@@ -490,15 +506,17 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
                       (descs[g].m < 0 || descs[g].m > t.hub_degree);
   if (hubs_possible)
     HIP_TRY(mmb::count_batch_hubs(descs_dev, vtx_dev, G, N, t.hub_degree, t.hub_chunk, ws, s));
-  // meshes (no list longer than kMeshDegree) get their own block length
-  const bool find_meshes = t.mesh_wave_vertices > 0;
+  // meshes (no list longer than kMeshDegree) get their own block length; a
+  // graph swept whole has no blocks
+  bool blocked = false;
+  for (int32_t g = 0; g < G && !blocked; ++g)
+    blocked = !(descs[g].flags & mmb::kWholeGraph) && descs[g].n > 0;
+  const bool find_meshes = t.mesh_wave_vertices > 0 && blocked;
   if (find_meshes) HIP_TRY(mmb::batch_find_meshes(descs_dev, vtx_dev, G, N, s));
   uint32_t hf = 0;
   unsigned long long n_pieces = 0;
-  HIP_TRY(hipMemcpyAsync(&hf, f, sizeof(hf), hipMemcpyDeviceToHost, s));
-  if (hubs_possible)
-    HIP_TRY(hipMemcpyAsync(&n_pieces, ws + kHubOffset, sizeof(n_pieces), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));  // the host vectors are released after this
+  if (flags & MM_VALIDATE) HIP_TRY(mmi::read_back(&hf, f, sizeof(hf), s));
+  if (hubs_possible) HIP_TRY(mmi::read_back(&n_pieces, ws + kHubOffset, sizeof(n_pieces), s));
   if (hf) {
     HIP_TRY(hipMemsetAsync(ws, 0, kCtrlBytes, s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -582,7 +600,8 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
   if (!items.empty()) {
     hipError_t e = hipMemcpyAsync(items_dev, items.data(), sizeof(mmb::WorkItem) * items.size(),
                                   hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host vector is released after this
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    uploads.waited = e == hipSuccess;
     if (e != hipSuccess) {
       mmi::free_owned(own);
       return fail(MM_ERR_HIP, "uploading the work items failed: %s", hipGetErrorString(e));
@@ -811,8 +830,7 @@ mm_status mm_batch_sync(mm_batch_handle b, void* stream) {
   if (!b) return fail(MM_ERR_INVALID_ARG, "batch handle is null");
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint32_t err = 0;
-  HIP_TRY(hipMemcpyAsync(&err, b->ws, sizeof(err), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(mmi::read_back(&err, b->ws, sizeof(err), s));
   if (err) {
     HIP_TRY(hipMemsetAsync(b->ws, 0, sizeof(uint32_t), s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -826,8 +844,7 @@ mm_status mm_batch_get_stats(mm_batch_handle b, void* stream, mm_stats* out) {
   if (!(b->flags & MM_STATS)) return fail(MM_ERR_UNSUPPORTED, "batch was created without MM_STATS");
   hipStream_t s = static_cast<hipStream_t>(stream);
   unsigned long long c[mmi::kStatWords] = {};
-  HIP_TRY(hipMemcpyAsync(c, b->ws + kStatsOffset, sizeof(c), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(mmi::read_back(c, b->ws + kStatsOffset, sizeof(c), s));
   mmi::stats_from_counters(c, out);
   return MM_OK;
 }

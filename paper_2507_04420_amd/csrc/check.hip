@@ -318,8 +318,7 @@ __global__ __launch_bounds__(kThreads) void check_batch_kernel(
 
 mm_status finish(unsigned long long* dev, hipStream_t s, int64_t* counts) {
   unsigned long long h[6];
-  HIP_TRY(hipMemcpyAsync(h, dev, sizeof(h), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(mmi::read_back(h, dev, sizeof(h), s));
   for (int k = 0; k < 6; ++k) counts[k] = (int64_t)h[k];
   return MM_OK;
 }

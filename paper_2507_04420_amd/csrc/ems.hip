@@ -201,8 +201,7 @@ mm_status mm_ems_run(mm_handle h, void* stream, uint64_t seed, void* scratch,
                          ctr);
       HIP_TRY(hipGetLastError());
       unsigned long long c[3];
-      HIP_TRY(hipMemcpyAsync(c, ctr, sizeof(c), hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipStreamSynchronize(s));
+      HIP_TRY(mmi::read_back(c, ctr, sizeof(c), s));
       ++iters;
       touched += (int64_t)c[0];
       pairs += (int64_t)c[2];

@@ -155,8 +155,7 @@ hipError_t build_typed(const OffT* off, int64_t n, int64_t hub_degree, int64_t c
                      chunk, total);
   e = hipGetLastError();
   ull host_total = 0;
-  if (e == hipSuccess) e = hipMemcpyAsync(&host_total, total, sizeof(ull), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess) e = mmi::read_back(&host_total, total, sizeof(ull), s);
   if (e != hipSuccess || host_total == 0) return e;
   e = hipMallocAsync(reinterpret_cast<void**>(table), sizeof(mmk::HubChunk) * (size_t)host_total, s);
   if (e != hipSuccess) {

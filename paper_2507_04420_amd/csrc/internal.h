@@ -102,6 +102,14 @@ inline int64_t short_blocks(int64_t sources, int64_t wave_vertices, int64_t min_
   return w < 64 ? 64 : w;
 }
 
+// Copies `bytes` (at most kReadBack) of device memory to host memory after the
+// work enqueued on s, and waits for it. The copy goes through a slot of a page
+// of pinned memory that the process keeps: into the caller's own (pageable)
+// memory the runtime would stage it, which takes 6 to 7 us longer (a check of
+// 65536 vertices 40.5 -> 34 us).
+constexpr size_t kReadBack = 256;
+hipError_t read_back(void* dst, const void* src, size_t bytes, hipStream_t s);
+
 // Copies the raw device counters (sweep.h order) into the ABI struct.
 void stats_from_counters(const unsigned long long* c, mm_stats* out);
 

@@ -107,6 +107,58 @@ size_t hint_bytes(int64_t n, const mm_tuning& t) {
   return round_up((size_t)hint_words(n, t.hint) * 4, 256);
 }
 
+namespace {
+
+// The pinned page: kSlots slots of kReadBack bytes, each held by one call at a
+// time. Made at the first use, for every device, and kept until the process
+// ends. A call that finds no page or no free slot copies without one.
+struct PinnedSlots {
+  static constexpr int kSlots = 16;
+  std::mutex mu;
+  uint8_t* page = nullptr;
+  bool tried = false;
+  uint32_t used = 0;
+  int take() {
+    std::lock_guard<std::mutex> lock(mu);
+    if (!tried) {
+      tried = true;
+      // another thread may be capturing a graph, which an allocation by this
+      // one must not end
+      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+      const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kSlots * kReadBack, hipHostMallocPortable) == hipSuccess)
+        page = static_cast<uint8_t*>(p);
+      else
+        (void)hipGetLastError();
+      if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    for (int k = 0; page && k < kSlots; ++k)
+      if (!(used >> k & 1u)) {
+        used |= 1u << k;
+        return k;
+      }
+    return -1;
+  }
+  void give(int k) {
+    std::lock_guard<std::mutex> lock(mu);
+    used &= ~(1u << k);
+  }
+};
+PinnedSlots g_pinned;
+
+}  // namespace
+
+hipError_t read_back(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  const int slot = bytes <= kReadBack ? g_pinned.take() : -1;
+  void* to = slot < 0 ? dst : g_pinned.page + slot * kReadBack;
+  hipError_t e = hipMemcpyAsync(to, src, bytes, hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess && slot >= 0) std::memcpy(dst, to, bytes);
+  if (slot >= 0) g_pinned.give(slot);
+  return e;
+}
+
 void stats_from_counters(const unsigned long long* c, mm_stats* out) {
   std::memset(out, 0, sizeof(*out));
   out->sources = c[S_SOURCES];
@@ -274,6 +326,10 @@ __device__ __forceinline__ void sweep_graph(SweepParams p, const OffT* __restric
   if (STATS) cnt.flush(stats);
 }
 
+// Seven wavefronts per SIMD (63 to 72 registers). The lanes' chains of
+// dependent memory operations are the bound, so what keeps registers free is
+// worth its instructions: with the block's bounds in registers of every lane
+// instead of scalars the sweep took 81 to 88, and five fitted.
 template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS>
 __global__ __launch_bounds__(256) void sweep_kernel(SweepParams p, const OffT* __restrict__ off,
                                                    const int32_t* __restrict__ nbr, int64_t n,
@@ -281,21 +337,6 @@ __global__ __launch_bounds__(256) void sweep_kernel(SweepParams p, const OffT* _
                                                    int64_t n_chunks,
                                                    const unsigned long long* chunk_count, Layout L,
                                                    unsigned long long* stats) {
-  sweep_graph<OffT, Layout, HINT, LAZY, STATS>(p, off, nbr, n, v_begin, main_waves, n_chunks,
-                                               chunk_count, L, stats);
-}
-
-// The same sweep compiled for at least six wavefronts per SIMD (tuning
-// occupancy = 6): at most 80 VGPRs, where the compiler alone takes 81 and
-// gets five. The lanes' chains of dependent memory operations are the
-// bound, so more wavefronts hide more of their latency; the graph's share in
-// flight grows too. Instantiated only for the sweeps that fit without spills
-// (not relabelled, not instrumented).
-template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void sweep_kernel_w6(
-    SweepParams p, const OffT* __restrict__ off, const int32_t* __restrict__ nbr, int64_t n,
-    int64_t v_begin, int64_t main_waves, int64_t n_chunks, const unsigned long long* chunk_count,
-    Layout L, unsigned long long* stats) {
   sweep_graph<OffT, Layout, HINT, LAZY, STATS>(p, off, nbr, n, v_begin, main_waves, n_chunks,
                                                chunk_count, L, stats);
 }
@@ -477,14 +518,9 @@ hipError_t launch_sweep(const mm_graph* g, const Layout& L, hipStream_t s) {
     hipError_t e = hipEventRecord(g->timing->before(), s);
     if (e != hipSuccess) return e;
   }
-  void (*kernel)(SweepParams, const OffT*, const int32_t*, int64_t, int64_t, int64_t, int64_t,
-                 const unsigned long long*, Layout, unsigned long long*) =
-      sweep_kernel<OffT, Layout, HINT, LAZY, STATS>;
-  if constexpr (!Layout::kRelabelled && !STATS) {
-    if (g->tun.occupancy == 6) kernel = sweep_kernel_w6<OffT, Layout, HINT, LAZY, STATS>;
-  }
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(g->tun.wg_size), lds, s, pl, off, nbr, g->n,
-                     v_begin, waves, g->n_chunks, g->chunk_count, L, stats);
+  hipLaunchKernelGGL((sweep_kernel<OffT, Layout, HINT, LAZY, STATS>), dim3((unsigned)blocks),
+                     dim3(g->tun.wg_size), lds, s, pl, off, nbr, g->n, v_begin, waves, g->n_chunks,
+                     g->chunk_count, L, stats);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (g->timing) {
@@ -758,8 +794,7 @@ mm_status mm_create(const void* offsets, mm_offset_type off_type, const int32_t*
                          static_cast<const int32_t*>(offsets), neighbors, n, m, f);
     HIP_TRY(hipGetLastError());
     uint32_t hf = 0;
-    HIP_TRY(hipMemcpyAsync(&hf, f, sizeof(hf), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(mmi::read_back(&hf, f, sizeof(hf), s));
     HIP_TRY(hipMemsetAsync(ws, 0, kCtrlBytes, s));
     if (hf) {
       return fail(MM_ERR_INVALID_GRAPH, "invalid CSR:%s%s%s",
@@ -963,8 +998,7 @@ mm_status mm_sync(mm_handle g, void* stream) {
   if (!g) return fail(MM_ERR_INVALID_ARG, "handle is null");
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint32_t err = 0;
-  HIP_TRY(hipMemcpyAsync(&err, g->ws, sizeof(err), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(mmi::read_back(&err, g->ws, sizeof(err), s));
   if (err) {
     HIP_TRY(hipMemsetAsync(g->ws, 0, sizeof(uint32_t), s));
     HIP_TRY(hipStreamSynchronize(s));
@@ -979,8 +1013,7 @@ mm_status mm_get_stats(mm_handle g, void* stream, mm_stats* out) {
   if (!(g->flags & MM_STATS)) return fail(MM_ERR_UNSUPPORTED, "handle was created without MM_STATS");
   hipStream_t s = static_cast<hipStream_t>(stream);
   unsigned long long c[kStatWords] = {};
-  HIP_TRY(hipMemcpyAsync(c, g->ws + kStatsOffset, sizeof(c), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(mmi::read_back(c, g->ws + kStatsOffset, sizeof(c), s));
   mmi::stats_from_counters(c, out);
   return MM_OK;
 }

@@ -113,8 +113,7 @@ mm_status mm_pairs(mm_handle h, void* stream, const int32_t* match, int32_t* pai
     HIP_TRY(hipGetLastError());
   }
   unsigned long long c = 0;
-  HIP_TRY(hipMemcpyAsync(&c, cursor, sizeof(c), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  HIP_TRY(mmi::read_back(&c, cursor, sizeof(c), s));
   *count = (int64_t)c;
   if ((int64_t)c > cap)
     return fail(MM_ERR_OUT_OF_MEMORY, "%lld pairs, buffer holds %lld (only the first %lld written)",
