@@ -80,6 +80,7 @@ def batch_tuning():
     t = autotune.tuned("batch")
     t.whole_graph_vertices = Tuning().whole_graph_vertices
     t.wait_release = 1
+    t.min_waves = Tuning().min_waves  # few lanes of a graph in flight at once (its spread)
     return t
 
 
