@@ -277,41 +277,6 @@ __device__ __forceinline__ void whole_loop(const SweepParams& a, GOff __restrict
     p_vw = n_vw;
     lds_order();
 
-    // ---------------- issue one operation per lane. The front end and the
-    // assist below only look at matched bits, which change above alone, so
-    // their work may come after it and under its latency
-    t = in(p_res) ? u : v;
-    if (__builtin_expect((p_mw | p_vw) != 0, 0)) {
-      if (in(p_mw | p_vw)) chk_v = st[v];
-      lds_order();
-    }
-    if (in(p_mat)) mat_w = reserve(t);
-    lds_order();
-    if (__builtin_expect(p_chk != 0, 0)) {
-      if (in(p_chk)) {
-        chk_u = st[u];
-        chk_v = st[v];
-      }
-      lds_order();
-    }
-    if (in(p_res)) res_w = reserve(t);
-    lds_order();
-    if (in(p_sts)) {
-      rd = cand & todo;
-      const uint32_t t0 = todo;
-      todo = 0;
-      if (in(p_sts & (one_all | (first & one_first)))) {
-        rd &= 0u - rd;  // the first candidate
-        todo = rd ? t0 & ~(rd | (rd - 1)) : 0u;  // the positions behind it
-      }
-      s0 = st[w.x];
-      s1 = st[w.y];
-      s2 = st[w.z];
-      s3 = st[w.w];
-    }
-    first &= ~p_sts;
-    lds_order();
-
     // ---------------- front end: queue the chunk whose states were read
     if (pending) {
       const uint64_t need = __ballot(fx < n) & __ballot(fb != fe) & __ballot(!(fw & kMch));
@@ -386,6 +351,42 @@ __device__ __forceinline__ void whole_loop(const SweepParams& a, GOff __restrict
       if (lane == 0) atomicOr(a.err, 1u);
       break;
     }
+
+    // ---------------- issue one operation per lane. The front end and the
+    // assist below only look at matched bits, which change above alone, so
+    // their work may come after it and under its latency; the sources handed
+    // out above are first looked at on the next trip
+    t = in(p_res) ? u : v;
+    if (__builtin_expect((p_mw | p_vw) != 0, 0)) {
+      if (in(p_mw | p_vw)) chk_v = st[v];
+      lds_order();
+    }
+    if (in(p_mat)) mat_w = reserve(t);
+    lds_order();
+    if (__builtin_expect(p_chk != 0, 0)) {
+      if (in(p_chk)) {
+        chk_u = st[u];
+        chk_v = st[v];
+      }
+      lds_order();
+    }
+    if (in(p_res)) res_w = reserve(t);
+    lds_order();
+    if (in(p_sts)) {
+      rd = cand & todo;
+      const uint32_t t0 = todo;
+      todo = 0;
+      if (in(p_sts & (one_all | (first & one_first)))) {
+        rd &= 0u - rd;  // the first candidate
+        todo = rd ? t0 & ~(rd | (rd - 1)) : 0u;  // the positions behind it
+      }
+      s0 = st[w.x];
+      s1 = st[w.y];
+      s2 = st[w.z];
+      s3 = st[w.w];
+    }
+    first &= ~p_sts;
+    lds_order();
 
     // ---------------- front end: read the states of the next chunk's sources
     if (chunk < stride && q_tail - q_head < 64) {
