@@ -263,6 +263,8 @@ hipError_t launch_whole_lds(const BatchPlan& bp, hipStream_t s) {
 template <bool STATS>
 hipError_t enqueue_typed(const BatchPlan& bp, hipStream_t s) {
   uint32_t* mate_w = reinterpret_cast<uint32_t*>(bp.mate);
+  // graphs kept in LDS only: their kernel writes the whole output
+  if (bp.n_items == 0) return launch_whole_lds<STATS>(bp, s);
   if (bp.hint) fill(bp.hint_base, bp.hint_words, 0u, s);
   hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(64), 0, s, bp.queue);
   const bool two = bp.protocol == MM_PROTOCOL_TWO_PHASE;

@@ -473,33 +473,30 @@ bool whole_in_lds(const mm_graph* g) {
          g->n <= MM_LDS_WHOLE_MAX;
 }
 
+// The whole pass of such a graph: the kernel keeps states and mates in LDS and
+// writes every entry of the output itself, so nothing is filled before it.
 template <typename OffT, bool STATS>
-hipError_t launch_whole_lds(const mm_graph* g, const SweepParams& p, int32_t* mate,
-                            unsigned long long* stats, hipStream_t s) {
+hipError_t launch_whole_lds(const mm_graph* g, int32_t* mate, hipStream_t s) {
+  if (g->timing) {
+    const hipError_t e = hipEventRecord(g->timing->before(), s);
+    if (e != hipSuccess) return e;
+  }
   const size_t shmem = sizeof(uint32_t) * (size_t)whole_lds_words(g->n);
-  hipLaunchKernelGGL((whole_lds_kernel<OffT, STATS>), dim3(1), dim3(64), shmem, s, p,
-                     static_cast<const OffT*>(g->off), g->nbr, g->n, mate, stats);
-  return hipGetLastError();
+  hipLaunchKernelGGL((whole_lds_kernel<OffT, STATS>), dim3(1), dim3(64), shmem, s, make_params(g),
+                     static_cast<const OffT*>(g->off), g->nbr, g->n, mate,
+                     reinterpret_cast<unsigned long long*>(g->ws + kStatsOffset));
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && g->timing) {
+    e = hipEventRecord(g->timing->after(), s);
+    ++g->timing->recorded;
+  }
+  return e;
 }
 
 template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS>
 hipError_t launch_sweep(const mm_graph* g, const Layout& L, hipStream_t s) {
   const SweepParams p = make_params(g);
   unsigned long long* stats = reinterpret_cast<unsigned long long*>(g->ws + kStatsOffset);
-  if constexpr (!Layout::kRelabelled) {
-    if (whole_in_lds(g)) {
-      if (g->timing) {
-        hipError_t e = hipEventRecord(g->timing->before(), s);
-        if (e != hipSuccess) return e;
-      }
-      hipError_t e = launch_whole_lds<OffT, STATS>(g, p, L.mate, stats, s);
-      if (e == hipSuccess && g->timing) {
-        e = hipEventRecord(g->timing->after(), s);
-        ++g->timing->recorded;
-      }
-      return e;
-    }
-  }
   const int64_t v_begin = sweep_begin(g);
   const OffT* off = g->relabel ? reinterpret_cast<const OffT*>(g->rl.off)
                                : static_cast<const OffT*>(g->off);
@@ -597,6 +594,7 @@ hipError_t run_relabelled(const mm_graph* g, int32_t* out, hipStream_t s) {
 
 template <typename OffT, bool STATS>
 hipError_t run_typed(const mm_graph* g, int32_t* mate, hipStream_t s) {
+  if (whole_in_lds(g)) return launch_whole_lds<OffT, STATS>(g, mate, s);
   const int64_t n = g->n;
   uint32_t* mate_w = reinterpret_cast<uint32_t*>(mate);
   Hint hint{g->hint(), hint_lg(g->tun.hint)};
