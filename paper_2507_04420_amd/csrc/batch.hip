@@ -177,7 +177,8 @@ __global__ __launch_bounds__(256) void batch_sweep_kernel(SweepParams p,
       }
     } else {
       pp.chunks = nullptr;
-      if (d.flags & kWholeGraph) {  // as mm_run sweeps a graph whole
+      pp.whole = (d.flags & kWholeGraph) != 0;
+      if (pp.whole) {  // as mm_run sweeps a graph whole
         pp.hub_degree = 0;
         pp.disperse = 1;
       } else if (d.flags & kMesh) {
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(256) void batch_sweep_kernel(SweepParams p,
       }
     }
     sweep_block<int64_t, Layout, HINT, LAZY, STATS>(pp, d.off, d.nbr, L, w.vb, nv, ring,
-                                                    wave_noted(ring, noted_sources(pp.disperse)), cnt);
+                                                    wave_noted(ring, noted_sources(pp)), cnt);
   }
   if (STATS) cnt.flush(stats);
 }
@@ -652,6 +653,7 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
   p.params.lower_stop = 0;  // no reordered copy of a batch's lists
   p.params.probe_first = t.probe_first;
   p.params.iter_cap = t.iter_cap;
+  p.params.whole = 0;
   p.params.hub_degree = n_chunks > 0 ? t.hub_degree : 0;
   p.params.hub_chunk = t.hub_chunk;
   p.params.chunks = chunks;

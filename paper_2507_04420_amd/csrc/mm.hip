@@ -289,7 +289,7 @@ __device__ __forceinline__ void sweep_graph(SweepParams p, const OffT* __restric
     __syncthreads();
   }
   const int64_t wave = uniform64(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const bool noted = noted_sources(p.disperse);
+  const bool noted = noted_sources(p);
   int64_t vb, nv;
   if (wave < main_waves) {
     vb = v_begin + wave * p.wave_vertices;
@@ -453,7 +453,8 @@ SweepParams make_params(const mm_graph* g) {
   p.hub_chunk = g->tun.hub_chunk;
   p.chunks = nullptr;
   const int64_t ns = g->n - sweep_begin(g);
-  if (ns <= g->tun.whole_graph_vertices) {  // one wavefront takes the whole graph
+  p.whole = ns <= g->tun.whole_graph_vertices;
+  if (p.whole) {  // one wavefront takes the whole graph
     p.wave_vertices = std::max<int64_t>(64, (ns + 63) / 64 * 64);
     // lanes stride apart: one wavefront alone is bound by its loop trips, and
     // lanes on adjacent vertices (neighbours in a mesh) would wait on each
@@ -509,7 +510,7 @@ hipError_t launch_sweep(const mm_graph* g, const Layout& L, hipStream_t s) {
   pl.chunks = g->chunks;
   const int wpb = g->tun.wg_size / 64;
   const int64_t blocks = (waves + chunk_waves + wpb - 1) / wpb;
-  const size_t lds = wpb * wave_lds_bytes(noted_sources(p.disperse));
+  const size_t lds = wpb * wave_lds_bytes(noted_sources(p));
   if (blocks == 0) return hipSuccess;
   if (g->timing) {
     hipError_t e = hipEventRecord(g->timing->before(), s);

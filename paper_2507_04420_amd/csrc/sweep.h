@@ -89,6 +89,8 @@ struct SweepParams {
                            // the first neighbour below the source; 0: no such order
   int32_t probe_first;     // 1: a source's first state read takes only its first candidate;
                            // 2: every state read takes one candidate
+  int32_t whole;           // 1: one block is a whole graph, whose result is that of this
+                           // schedule alone: nothing may change when a lane does what
   int64_t iter_cap;        // 0: per-block default budget
   uint32_t* err;           // bit 0: loop-trip budget exceeded
   // Hub tier. Main pass: sources with more than hub_degree entries are left
@@ -187,7 +189,9 @@ __host__ __device__ __forceinline__ size_t wave_lds_bytes(bool noted) {
 // 3.8e6 of 8.8e6 reservations (322 -> 255 us with the guess on a shared word),
 // while on graphs whose edges leave the block they cost more than they find (ER
 // of 4e6 vertices 314 -> 326 us, R-MAT-25 809 -> 820).
-__host__ __device__ __forceinline__ bool noted_sources(int32_t disperse) { return disperse != 0; }
+__host__ __device__ __forceinline__ bool noted_sources(const SweepParams& p) {
+  return p.disperse && !p.whole;
+}
 
 // This wavefront's ring in the workgroup's dynamic LDS, and its bits, or null.
 __device__ __forceinline__ QSlot* wave_ring(void* lds, bool noted) {
@@ -398,7 +402,7 @@ __device__ __forceinline__ void sweep_block(const SweepParams& a, OffP __restric
         if (s == R_ACC) {
           // taking u has changed v's word too if they share one
           if constexpr (!Layout::kTwoPhase && !Layout::kStateIsMate) {
-            if (L.wp(u) == L.wp(v)) vguess = res_w | (1u << Layout::shift(u));
+            if (!a.whole && L.wp(u) == L.wp(v)) vguess = res_w | (1u << Layout::shift(u));
           }
           phase = P_MAT;
         } else if (s == R_MCHD) {

@@ -2,6 +2,8 @@
 own that the plain build runs has the schedule of the general sweep, which the
 instrumented build runs, so the two give the same mates, entry by entry, and
 the counters of the one describe the other."""
+import hashlib
+
 import numpy as np
 import pytest
 
@@ -107,3 +109,53 @@ def test_whole_loop_budget():
     v = np.flatnonzero(mate >= 0)
     assert len(v) and np.array_equal(mate[mate[v]], v)
     g.close()
+
+
+# one wavefront with its states in device memory: the matching is that of the
+# schedule alone, so what several wavefronts share a sweep by (noted sources,
+# the guess on a shared word) must leave it as it was
+WHOLE_PINS = {
+    ("er5003", "u8_cas"): "dd7c835c81fbf2d4",
+    ("er5003", "u2_two"): "74e44f21c5cc2317",
+    ("er5003", "u32_cas"): "d5fd7bd0aa5263e2",
+    ("er5003", "u8_hint_upper"): "02edf171caa199b4",
+    ("er5003", "u8_relabel"): "8446d6584d0716b5",
+    ("grid127x129", "u8_cas"): "31059041ea52c699",
+    ("grid127x129", "u2_two"): "baee8bc2dda2f152",
+    ("grid127x129", "u32_cas"): "baee8bc2dda2f152",
+    ("grid127x129", "u8_hint_upper"): "31f3839783ed7d29",
+    ("grid127x129", "u8_relabel"): "57ab1fefec1eb504",
+    ("rmat13", "u8_cas"): "07c26d0e6f7e62a5",
+    ("rmat13", "u2_two"): "10015fd4b129255e",
+    ("rmat13", "u32_cas"): "3735ae67668a33b9",
+    ("rmat13", "u8_hint_upper"): "4ed7934b9f9b8027",
+    ("rmat13", "u8_relabel"): "d7539135304c8648",
+}
+WHOLE_TUNINGS = {
+    "u8_cas": dict(layout=0),
+    "u2_two": dict(layout=2, protocol=1),
+    "u32_cas": dict(),
+    "u8_hint_upper": dict(layout=0, hint=2, upper_only=1, wait_release=1),
+    "u8_relabel": dict(layout=0, relabel=1),
+}
+WHOLE_GRAPHS = {
+    "er5003": lambda: graphgen.er(5003, 12.0, seed=6),
+    "grid127x129": lambda: graphgen.grid(127, 129),
+    "rmat13": lambda: graphgen.rmat(13, 8, seed=8),
+}
+
+
+@pytest.mark.parametrize("graph,tuning", list(WHOLE_PINS))
+def test_whole_in_device_memory_keeps_its_schedule(graph, tuning):
+    g = WHOLE_GRAPHS[graph]()
+    t = mm.Tuning.default()
+    t.whole_graph_lds = 0
+    for k, v in WHOLE_TUNINGS[tuning].items():
+        setattr(t, k, v)
+    h = mm.Graph(torch.from_numpy(g.off).cuda(), torch.from_numpy(g.nbr).cuda(),
+                 symmetric=True, tuning=t)
+    for _ in range(2):
+        mate = h.run().cpu().numpy()
+        assert hashlib.sha1(mate.tobytes()).hexdigest()[:16] == WHOLE_PINS[graph, tuning]
+    h.sync()
+    h.close()
