@@ -32,22 +32,41 @@ constexpr int64_t kOwnList = 32;
 // a random access, to a line of a mate array far larger than the 4 MB of an
 // XCD's L2, or to a bit of an array that fits it. The bits cost a pass over the
 // mates and an allocation (15 to 25 us), so below 2^23 vertices or on sparse
-// graphs, whose scans are few or local, they do not pay: check_kernel and
-// bits together, without and with, R-MAT-25 920 and 616 us, R-MAT-24 460 and 373,
-// ER of 2^24 vertices and 8 entries each 405 and 394; but ER of 2^22 and 16
-// 138 and 151, a mesh of 1e7 115 and 140.
+// graphs, whose scans are few or local, they do not pay or not always. The call
+// without and with them: R-MAT-25 951 and 671 us, R-MAT-24 460 and 373, ER of
+// 2^24 vertices and 8 entries each 409 and 382, of 2^22 and 16 131 and 128; but a mesh
+// of 1e7 96 and 118.
 constexpr int64_t kBitsFrom = (int64_t)1 << 23;
 constexpr int64_t kBitsDegree = 8;
 constexpr int kThreads = 1024;
 constexpr int kWindow = 256;  // laid-out entries a wavefront takes per step, four a lane
 
-// One list to examine: for y >= 0, whether it holds y; else (x is unmatched)
-// how many of its entries lead to other unmatched vertices.
-struct List {
-  const int32_t* p;  // its first entry
-  const void* free;  // the list's graph: its mates, or (BITS) a bit per vertex, set if unmatched
-  int32_t n, x, y;
-  int32_t start;        // position of its first entry in the laid-out order
+// Loads are typed as global ones. Through generic pointers (a batch's graphs
+// keep theirs in memory, a list's place comes from LDS) they would count as LDS
+// operations too, and every LDS read would wait for the loads before it.
+template <typename T>
+using Global = const __attribute__((address_space(1))) T*;
+
+// An id is read once; with BITS it must not push the bits out of L2 (the call,
+// R-MAT-25 685 -> 671 us, R-MAT-24 unchanged; offsets read so as well took
+// R-MAT-25 to 655 and R-MAT-24 from 372 to 389).
+template <bool BITS>
+__device__ __forceinline__ int32_t load_id(Global<int32_t> p) {
+  return BITS ? __builtin_nontemporal_load(p) : *p;
+}
+
+// What the lists of a call lead to, the same for all lanes.
+struct Ids {
+  Global<int32_t> nbr;
+  Global<uint32_t> free;  // mates, or (BITS) a bit per vertex, set if unmatched
+  uint32_t n;             // vertices
+};
+
+// One list to examine: for key >= 0, whether it holds key; else, the list of the
+// unmatched vertex ~key, how many of its entries lead to other unmatched vertices.
+struct alignas(16) List {
+  int64_t first;  // its first entry; laid end to end: less its first position
+  int32_t key;
 };
 
 // One wavefront's LDS.
@@ -62,10 +81,22 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
                                    __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Of four entries a lane, how many lead to an unmatched vertex; only those with
+// look[q] (which have an id in range) are read, all of them before the first is
+// looked at.
 template <bool BITS>
-__device__ __forceinline__ bool unmatched(const void* free, int32_t v) {
-  if (BITS) return (static_cast<const uint32_t*>(free)[v >> 5] >> (v & 31)) & 1u;
-  return static_cast<const int32_t*>(free)[v] == -1;
+__device__ __forceinline__ uint32_t unmatched(Global<uint32_t> free, const int32_t id[4],
+                                              const bool look[4]) {
+  uint32_t v[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    v[q] = 0;
+    if (look[q]) v[q] = free[BITS ? (uint32_t)id[q] >> 5 : (uint32_t)id[q]];
+  }
+  uint32_t sum = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sum += BITS ? (v[q] >> (id[q] & 31)) & 1u : (uint32_t)(v[q] == ~0u);
+  return sum;
 }
 
 // LDS written by one lane is read by another lane of the same wavefront.
@@ -75,7 +106,7 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // Examines one list per lane (len <= 0: none) with the whole wavefront.
-// Returns whether this lane's list holds its y; adds the uncovered entries of
+// Returns whether this lane's list holds its key; adds the uncovered entries of
 // the others to *uncovered.
 //
 // The lists are laid end to end and taken kWindow entries at a time: every
@@ -83,13 +114,21 @@ __device__ __forceinline__ void wave_sync() {
 // lengths, so that a long list does not hold the other 63 lanes and the loads
 // of a step are independent. The list an entry belongs to is the count of
 // list starts up to it: starts are marked in LDS and counted with a ballot.
+//
+// With few entries per vertex its instructions bound it, on large graphs the
+// random reads. What describes the call (Ids) is the same for all lanes and
+// stays in scalar registers, a list is one 16-byte LDS read, the loads of a
+// step are all issued before the first is waited for, and the kernels fit 64
+// registers without spills, so two workgroups share a CU. Against a list that
+// names its graph and generic pointers, the call: a mesh of 1e7 vertices
+// 120 -> 96 us, ER of 2^22 vertices and 16 entries each 136 -> 131, R-MAT-25 683 -> 671;
+// with two registers spilled ER took 158.
 template <bool BITS>
-__device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLds& w,
-                                           unsigned long long* uncovered) {
+__device__ __forceinline__ bool scan_lists(const Ids& g, const List& mine, int64_t len, WaveLds& w,
+                                           int32_t* uncovered) {
   const int lane = (int)(threadIdx.x & 63);
   const bool flat = len > 0 && len <= kFlatList;
   const uint64_t fm = __ballot(flat);
-  const uint64_t below_or_self = (2ull << lane) - 1;
   bool hit = false;
   if (fm) {
     // inclusive prefix sum of the flat lists' lengths
@@ -99,13 +138,11 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
       const int32_t o = __shfl_up(sum, d, 64);
       if (lane >= d) sum += o;
     }
-    const int32_t total = __shfl(sum, 63, 64);
+    const int32_t total = __builtin_amdgcn_readlane(sum, 63);
     const int32_t start = sum - (flat ? (int32_t)len : 0);
     const uint32_t slot = lanes_below(fm);
     if (flat) {
-      List l = mine;
-      l.start = start;
-      w.list[slot] = l;
+      w.list[slot] = List{mine.first - start, mine.key};
       w.found[slot] = 0;
     }
     int32_t before = -1;  // lists started before the window, less one
@@ -115,27 +152,31 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
       if (flat && start >= base && start < base + kWindow)
         reinterpret_cast<uint8_t*>(w.head)[start - base] = 1;
       wave_sync();
-      int32_t id[4];
-      int at[4];
+      int32_t id[4], at[4];
+      List l[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const uint64_t h = __ballot(reinterpret_cast<const uint8_t*>(w.head)[q * 64 + lane] != 0);
-        at[q] = before + (int)__popcll(h & below_or_self);
-        before += (int)__popcll(h);
+        const int32_t starts = reinterpret_cast<const uint8_t*>(w.head)[q * 64 + lane];
+        const uint64_t h = __ballot(starts != 0);
+        at[q] = before + starts + (int32_t)lanes_below(h);
+        before += (int32_t)__popcll(h);
+        l[q] = w.list[at[q]];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
         const int32_t pos = base + q * 64 + lane;
-        id[q] = pos < total ? w.list[at[q]].p[pos - w.list[at[q]].start] : -1;
+        id[q] = -1;
+        if (pos < total) id[q] = load_id<BITS>(g.nbr + (l[q].first + pos));
       }
       wave_sync();
+      bool look[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        if (base + q * 64 + lane >= total) continue;
-        const List& l = w.list[at[q]];
-        if (l.y >= 0) {
-          if (id[q] == l.y) w.found[at[q]] = 1;
-        } else if (id[q] >= 0 && id[q] < l.n && id[q] != l.x) {
-          *uncovered += unmatched<BITS>(l.free, id[q]);
-        }
+        const bool in = (uint32_t)id[q] < g.n;
+        if (in && id[q] == l[q].key) w.found[at[q]] = 1;
+        look[q] = in && l[q].key < 0 && id[q] != ~l[q].key;
       }
+      *uncovered += (int32_t)unmatched<BITS>(g.free, id, look);
     }
     wave_sync();
     hit = flat && w.found[slot] != 0;
@@ -145,21 +186,24 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
   while (longs) {
     const int src = __builtin_ctzll(longs);
     longs &= longs - 1;
-    const int32_t* p = reinterpret_cast<const int32_t*>(__shfl((long long)mine.p, src, 64));
-    const void* free = reinterpret_cast<const void*>(__shfl((long long)mine.free, src, 64));
+    const int64_t first = __shfl((long long)mine.first, src, 64);
     const int64_t m = __shfl((long long)len, src, 64);
-    const int32_t n = __shfl(mine.n, src, 64), x = __shfl(mine.x, src, 64), y = __shfl(mine.y, src, 64);
+    const int32_t key = __shfl(mine.key, src, 64);
     bool any = false;
     for (int64_t i = 0; i < m && !any; i += kWindow) {
       int32_t id[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) id[q] = i + q * 64 + lane < m ? p[i + q * 64 + lane] : -1;
-      if (y >= 0) {
-        any = __ballot(id[0] == y || id[1] == y || id[2] == y || id[3] == y) != 0;
+      for (int q = 0; q < 4; ++q) {
+        id[q] = -1;
+        if (i + q * 64 + lane < m) id[q] = load_id<BITS>(g.nbr + (first + i + q * 64 + lane));
+      }
+      if (key >= 0) {
+        any = __ballot(id[0] == key || id[1] == key || id[2] == key || id[3] == key) != 0;
       } else {
+        bool look[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (id[q] >= 0 && id[q] < n && id[q] != x) *uncovered += unmatched<BITS>(free, id[q]);
+        for (int q = 0; q < 4; ++q) look[q] = (uint32_t)id[q] < g.n && id[q] != ~key;
+        *uncovered += (int32_t)unmatched<BITS>(g.free, id, look);
       }
     }
     if (lane == src) hit = any;
@@ -167,6 +211,9 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
   return hit;
 }
 
+// Counts are 32 bits a lane (c[2] may be negative in between): the entries a lane
+// looks at are a 64th of its wavefront's, and 288 GB hold 7.2e10.
+//
 // Checks 64 vertices, one per lane (valid: the lane has one): vertex x of a
 // graph of n vertices whose offsets, ids and mates are based at its first
 // vertex; free: the mates again, or (BITS) its bits of unmatched vertices.
@@ -182,10 +229,13 @@ __device__ __forceinline__ bool scan_lists(const List& mine, int64_t len, WaveLd
 // that searches counts for both. An edge not found there is searched in the
 // other list (one-sided input).
 template <typename OffT, bool BITS>
-__device__ __forceinline__ void check_vertices(const OffT* off, const int32_t* nbr, int64_t n,
-                                               const int32_t* mate, const void* free, int64_t x,
-                                               bool valid, WaveLds& w, unsigned long long c[6]) {
-  List l{nullptr, free, (int32_t)n, (int32_t)x, -1, 0};
+__device__ __forceinline__ void check_vertices(const OffT* offsets, const int32_t* nbr, int64_t n,
+                                               const int32_t* mates, const void* free, int64_t x,
+                                               bool valid, WaveLds& w, int32_t c[6]) {
+  const Global<OffT> off = (Global<OffT>)offsets;
+  const Global<int32_t> mate = (Global<int32_t>)mates;
+  const Ids g{(Global<int32_t>)nbr, (Global<uint32_t>)free, (uint32_t)n};
+  List l{0, ~(int32_t)x};
   int64_t len = 0;
   unsigned weight = 1;
   bool search = false;
@@ -211,38 +261,38 @@ __device__ __forceinline__ void check_vertices(const OffT* off, const int32_t* n
         else
           weight = 2;  // the mate's list is longer: it leaves the search to this end
       }
-      l.y = (int32_t)y;
+      l.key = (int32_t)y;
     }
     if (search || y == -1) {
-      l.p = nbr + b;
+      l.first = b;
       len = e - b;
     }
   }
-  bool hit = scan_lists<BITS>(l, len, w, &c[4]);
+  bool hit = scan_lists<BITS>(g, l, len, w, &c[4]);
   const bool again = search && !hit;
   if (!__ballot(again)) return;
   len = 0;
   if (again) {
-    const int64_t y = l.y, b = (int64_t)off[y], e = (int64_t)off[y + 1];
+    const int64_t y = l.key, b = (int64_t)off[y], e = (int64_t)off[y + 1];
     // a mate with a long list has left the search to this end
     if (weight == 1 && e - b > kOwnList && (int64_t)mate[y] == x) weight = 2;
-    l.y = (int32_t)x;
-    l.p = nbr + b;
+    l.key = (int32_t)x;
+    l.first = b;
     len = e - b;
   }
-  hit = scan_lists<BITS>(l, len, w, &c[4]);
-  if (again && !hit) c[3] += weight;
+  hit = scan_lists<BITS>(g, l, len, w, &c[4]);
+  if (again && !hit) c[3] += (int32_t)weight;
 }
 
 // Sums the block's counts and adds them to out, one atomic per nonzero count
 // and block: atomics of all blocks on the same six words are done one after
 // the other, about 12 ns each.
-__device__ __forceinline__ void flush_counts(unsigned long long c[6], unsigned long long* out) {
+__device__ __forceinline__ void flush_counts(int32_t c[6], unsigned long long* out) {
   __shared__ unsigned long long part[kThreads / 64][6];
   const int lane = (int)(threadIdx.x & 63);
 #pragma unroll
   for (int k = 0; k < 6; ++k) {
-    unsigned long long s = c[k];
+    unsigned long long s = (unsigned long long)(long long)c[k];
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
     if (lane == 0) part[threadIdx.x >> 6][k] = s;
@@ -268,13 +318,11 @@ __global__ void free_bits_kernel(const int32_t* __restrict__ mate, int64_t n,
 }
 
 template <typename OffT, bool BITS>
-__global__ __launch_bounds__(kThreads) void check_kernel(const OffT* __restrict__ off,
-                                                         const int32_t* __restrict__ nbr, int64_t n,
-                                                         const int32_t* __restrict__ mate,
-                                                         const void* __restrict__ free,
-                                                         unsigned long long* out) {
+__global__ __launch_bounds__(kThreads) void check_kernel(
+    const OffT* __restrict__ off, const int32_t* __restrict__ nbr, int64_t n,
+    const int32_t* __restrict__ mate, const void* __restrict__ free, unsigned long long* out) {
   __shared__ WaveLds lds[kThreads / 64];
-  unsigned long long c[6] = {0, 0, 0, 0, 0, 0};
+  int32_t c[6] = {0, 0, 0, 0, 0, 0};
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
        x - (int64_t)(threadIdx.x & 63) < n; x += stride)
@@ -302,7 +350,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
     const mmb::GraphDesc* __restrict__ descs, const int64_t* __restrict__ vtx_off,
     int32_t num_graphs, const int32_t* __restrict__ mate, unsigned long long* out) {
   __shared__ WaveLds lds[kThreads / 64];
-  unsigned long long c[6] = {0, 0, 0, 0, 0, 0};
+  int32_t c[6] = {0, 0, 0, 0, 0, 0};
   const int64_t N = vtx_off[num_graphs];
   const int lane = (int)(threadIdx.x & 63);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
