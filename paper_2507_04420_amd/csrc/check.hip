@@ -344,8 +344,9 @@ __device__ __forceinline__ int graph_of(const int64_t* vtx_off, int lo, int hi, 
 // The wavefront takes the lanes of one graph at a time, so that the search for
 // it and what describes it stay in scalar registers: with a graph per lane the
 // kernel took 73 registers, of which one workgroup of 16 wavefronts fits a CU
-// (267 us for 256 graphs of 8.5e6 vertices in all; two fit now, 175 us; 1024 small
-// graphs 151 and 131 us with the call around it).
+// (267 us for 256 graphs of 8.5e6 vertices in all; two fit now, 175 us, and 152 with
+// the loads of scan_lists as they are; 1024 small graphs 151 and 131 us with the
+// call around it).
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void check_batch_kernel(
     const mmb::GraphDesc* __restrict__ descs, const int64_t* __restrict__ vtx_off,
     int32_t num_graphs, const int32_t* __restrict__ mate, unsigned long long* out) {
