@@ -79,6 +79,10 @@ hipError_t validate_list(const GraphDesc* descs, const int64_t* vtx_off_dev, int
 // 32-bit words of packed state for n vertices under `layout` (0 for words).
 int64_t state_words_for(int64_t n, int32_t layout);
 
+// The device check treats 64 consecutive vertices that belong to more graphs
+// than this apart (check.hip).
+constexpr int kCrowd = 8;
+
 // What the device check needs from a batch handle (all device pointers).
 struct BatchInfo {
   const GraphDesc* descs;
@@ -86,6 +90,7 @@ struct BatchInfo {
   int32_t G;
   int64_t N;
   uint8_t* ws;
+  bool crowded;  // some 64 consecutive vertices may belong to more than kCrowd graphs
 };
 BatchInfo batch_info(const mm_batch* b);
 

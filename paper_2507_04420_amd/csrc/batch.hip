@@ -404,6 +404,7 @@ struct mm_batch {
   mm_tuning tun;
   BatchLayout lay;
   std::vector<int64_t> vtx_off;
+  bool crowded;  // see BatchInfo
   mmb::BatchPlan plan;
   int32_t* bound_mate = nullptr;  // output the captured pass writes to
   hipStream_t cap_stream = nullptr;
@@ -641,6 +642,9 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
   b->tun = t;
   b->lay = lay;
   b->vtx_off = vtx;
+  b->crowded = false;
+  for (int32_t g = 0; g + mmb::kCrowd <= G && !b->crowded; ++g)
+    b->crowded = vtx[g + mmb::kCrowd] - vtx[g + 1] < 63;
   mmb::BatchPlan& p = b->plan;
   p.params.wave_vertices = lay.wave_vertices;
   p.params.disperse = t.disperse;
@@ -878,6 +882,7 @@ BatchInfo batch_info(const mm_batch* b) {
   i.G = b->G;
   i.N = b->N;
   i.ws = b->ws;
+  i.crowded = b->crowded;
   return i;
 }
 }  // namespace mmb

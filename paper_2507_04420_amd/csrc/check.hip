@@ -26,6 +26,9 @@ constexpr int64_t kFlatList = 2048;
 // A matched vertex whose list is longer than this leaves the search for its
 // edge to its mate when the mate's list is shorter.
 constexpr int64_t kOwnList = 32;
+// Entries of a graph whose vertices are checked by a lane each (check_alone): all
+// that 64 vertices can have without duplicates.
+constexpr int64_t kAlone = 64 * 64;
 // Single graphs of at least kBitsFrom vertices and kBitsDegree entries per
 // vertex get a bit per vertex for the scans of unmatched vertices: on a skewed
 // graph a quarter of the vertices stay unmatched, and every entry of theirs is
@@ -340,6 +343,48 @@ __device__ __forceinline__ int graph_of(const int64_t* vtx_off, int lo, int hi, 
   return lo;
 }
 
+// The same where the graph is lo or one of the next few.
+__device__ __forceinline__ int graph_from(const int64_t* vtx_off, int lo, int hi, int64_t v) {
+  int64_t at = lo, step = 1;
+  while (at + step < hi && vtx_off[at + step] <= v) {
+    at += step;
+    step *= 2;
+  }
+  return graph_of(vtx_off, (int)at, (int)(at + step < hi ? at + step : hi), v);
+}
+
+// One vertex of a small graph, checked by its lane alone.
+__device__ __forceinline__ void check_alone(const mmb::GraphDesc& d, const int32_t* mates, int64_t x,
+                                            int32_t c[6]) {
+  const Global<int64_t> off = (Global<int64_t>)d.off;
+  const Global<int32_t> nbr = (Global<int32_t>)d.nbr;
+  const Global<int32_t> mate = (Global<int32_t>)mates;
+  const int64_t y = mate[x];
+  int64_t b = off[x], e = off[x + 1];
+  if (y < -1 || y >= d.n) {
+    ++c[0];
+  } else if (y == x) {
+    ++c[1];
+    ++c[5];
+  } else if (y >= 0) {
+    bool edge = false;
+    for (; b < e && !edge; ++b) edge = nbr[b] == y;
+    if (!edge) {
+      b = off[y];
+      e = off[y + 1];
+      for (; b < e && !edge; ++b) edge = nbr[b] == x;
+    }
+    ++c[5];
+    c[2] += mate[y] != x;
+    c[3] += !edge;
+  } else {
+    for (; b < e; ++b) {
+      const int64_t z = nbr[b];
+      if (z >= 0 && z < d.n && z != x) c[4] += mate[z] == -1;
+    }
+  }
+}
+
 // A batch: 64 consecutive vertices lie in one graph unless it ends among them.
 // The wavefront takes the lanes of one graph at a time, so that the search for
 // it and what describes it stay in scalar registers: with a graph per lane the
@@ -347,6 +392,16 @@ __device__ __forceinline__ int graph_of(const int64_t* vtx_off, int lo, int hi, 
 // (267 us for 256 graphs of 8.5e6 vertices in all; two fit now, 175 us, and 152 with
 // the loads of scan_lists as they are; 1024 small graphs 151 and 131 us with the
 // call around it).
+//
+// CROWDED: some 64 consecutive vertices may belong to more than kCrowd graphs. One
+// graph after the other would then leave most lanes idle, so the lanes of such a
+// wavefront look up their own graphs and check alone the vertices of those that
+// lie within it whole (check_vertices counts for both ends of a pair, so a graph
+// goes one way or the other) and have at most kAlone entries; the others go on
+// as above. The call without and with it: 1e6 graphs of 1 to 8 vertices 917 and 169
+// us, 5e5 of one vertex 366 and 45, 1e5 of 1 to 16 130 and 77; of 8 to 16, seldom
+// as crowded, 117 and 84, which is the search that starts at the graph before.
+template <bool CROWDED>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void check_batch_kernel(
     const mmb::GraphDesc* __restrict__ descs, const int64_t* __restrict__ vtx_off,
     int32_t num_graphs, const int32_t* __restrict__ mate, unsigned long long* out) {
@@ -360,14 +415,24 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
     const int64_t first = ((int64_t)__builtin_amdgcn_readfirstlane((int)((v - lane) >> 32)) << 32) |
                           (uint32_t)__builtin_amdgcn_readfirstlane((int)(v - lane));
     uint64_t todo = __ballot(v < N);
-    for (int lo = 0; todo;) {
-      const int g = graph_of(vtx_off, lo, num_graphs, first + __builtin_ctzll(todo));
+    int g = graph_of(vtx_off, 0, num_graphs, first);
+    if (CROWDED && g + mmb::kCrowd <= num_graphs && vtx_off[g + mmb::kCrowd] < first + 64) {
+      bool done = false;
+      if (v < N) {
+        const mmb::GraphDesc& d = descs[graph_from(vtx_off, g, num_graphs, v)];
+        done = d.v0 >= first && d.v0 + d.n <= first + 64 && d.off[d.n] - d.off[0] <= kAlone;
+        if (done) check_alone(d, mate + d.v0, v - d.v0, c);
+      }
+      todo &= ~__ballot(done);
+      if (todo) g = graph_from(vtx_off, g, num_graphs, first + __builtin_ctzll(todo));
+    }
+    while (todo) {
       const mmb::GraphDesc& d = descs[g];
       const int32_t* m = mate + d.v0;
       const bool mine = ((todo >> lane) & 1) && v - d.v0 < d.n;
       check_vertices<int64_t, false>(d.off, d.nbr, d.n, m, m, v - d.v0, mine, lds[threadIdx.x >> 6], c);
       todo &= ~__ballot(mine);
-      lo = g + 1;
+      if (todo) g = graph_from(vtx_off, g + 1, num_graphs, first + __builtin_ctzll(todo));
     }
   }
   flush_counts(c, out);
@@ -447,8 +512,9 @@ mm_status mm_batch_check(mm_batch_handle b, void* stream, const int32_t* match, 
   HIP_TRY(hipMemsetAsync(dev, 0, 6 * sizeof(unsigned long long), s));
   if (info.N > 0) {
     const Grid gr = grid_of(info.N);
-    hipLaunchKernelGGL(check_batch_kernel, dim3(gr.blocks), dim3(gr.threads), 0, s, info.descs,
-                       info.vtx_off, info.G, match, dev);
+    const auto kernel = info.crowded ? check_batch_kernel<true> : check_batch_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3(gr.blocks), dim3(gr.threads), 0, s, info.descs, info.vtx_off,
+                       info.G, match, dev);
     HIP_TRY(hipGetLastError());
   }
   return finish(dev, s, counts);

@@ -2,6 +2,7 @@
 checker, on mate arrays built on the CPU: the oracle's own SGMM output and
 seeded corruptions of it, one per violation class of Section II-B plus mixed
 ones. Both checkers see the same array; their counts must be equal."""
+import time
 import zlib
 
 import numpy as np
@@ -201,4 +202,78 @@ def test_batch_check_ragged_members():
     want = [oracle.check(p, mt) for p, mt in zip(parts, mates)]
     for gf, wf in FIELDS:
         assert got[gf] == sum(getattr(w, wf) for w in want), (gf, got, want)
+    b.close()
+
+
+def many_members(sizes, seed, heavy=()):
+    """Members of the given sizes, each a random graph; those listed in heavy
+    hold every entry 600 times, so that their lists are long for their size."""
+    off, nbr, parts = [0], [], []
+    rng = np.random.default_rng(seed)
+    for k, n in enumerate(sizes):
+        e = rng.integers(0, max(n, 1), size=(n, 2))
+        p = graphgen.from_edges(n, np.repeat(e, 600, axis=0) if k in heavy else e, dedup=False)
+        off += (p.off[1:] + off[-1]).tolist()
+        nbr.append(p.nbr)
+        parts.append(p)
+    vtx = np.concatenate([[0], np.cumsum(sizes)])
+    return parts, np.array(off, dtype=np.int64), np.concatenate(nbr), vtx
+
+
+# more graphs than lanes take in turns among 64 vertices: small ones, empty
+# ones, long lists, and a large graph that ends or begins between them
+@pytest.mark.parametrize("layout", ["ones", "small", "between_large", "empties", "sixties"])
+def test_batch_check_crowded_members(layout):
+    rng = np.random.default_rng(3)
+    sizes = {
+        "ones": [1] * 700,
+        "small": rng.integers(1, 9, size=900).tolist(),
+        "between_large": [3000] + [2] * 31 + [500] + [3, 1, 4] * 9 + [65, 64, 63] + [1] * 9 + [2000],
+        "empties": [0, 0, 5] * 40 + [0] * 200 + [7] * 12 + [0] * 70,
+        "sixties": [64, 1, 1, 1, 1, 1, 1, 1, 1, 63, 2] * 12,
+    }[layout]
+    parts, off, nbr, vtx = many_members(sizes, 17, heavy=range(0, len(sizes), 5))
+    b = mm.Batch(torch.from_numpy(off).cuda(), torch.from_numpy(nbr).cuda(), vtx, symmetric=True)
+    for kind in range(3):
+        mates = []
+        for p in parts:
+            if p.n == 0:
+                continue
+            m = oracle.sgmm(p).mate.copy()
+            if kind == 1:
+                m[rng.random(p.n) < 0.3] = -1
+            elif kind == 2:
+                k = rng.random(p.n) < 0.4
+                m[k] = rng.integers(-2, p.n + 1, size=int(k.sum()))
+            mates.append(m)
+        got = b.check(torch.from_numpy(np.concatenate(mates)).cuda())
+        want = [oracle.check(p, m) for p, m in zip([p for p in parts if p.n], mates)]
+        for gf, wf in FIELDS:
+            assert got[gf] == sum(getattr(w, wf) for w in want), (layout, kind, gf)
+    b.close()
+
+
+def median_us(call, reps=15):
+    call()
+    times = []
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        call()
+        times.append(time.perf_counter() - t)
+    return 1e6 * sorted(times)[reps // 2]
+
+
+def test_batch_check_of_tiny_members_costs_as_one_graph():
+    # 5e5 graphs of one vertex against one graph of as many: one graph at a time
+    # took 9 times as long, and 1.2 times with the lanes side by side
+    n = 500000
+    off = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    nbr = torch.zeros(0, dtype=torch.int32, device="cuda")
+    mate = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    b, g = mm.Batch(off, nbr, np.arange(n + 1)), mm.Graph(off, nbr)
+    assert b.check(mate)["ok"] and g.check(mate)["ok"]
+    many, one = median_us(lambda: b.check(mate)), median_us(lambda: g.check(mate))
+    print("%.0f us for %d members, %.0f us for one graph" % (many, n, one))
+    assert many < 3 * one
     b.close()
