@@ -20,9 +20,15 @@ using mmi::fail;
 namespace {
 
 // Lists longer than this are checked by the whole wavefront, one after the
-// other; those up to it are laid end to end (scan_lists). It also bounds the
-// laid-out length of a wavefront's 64 lists, which then fits 32 bits.
-constexpr int64_t kFlatList = 2048;
+// other; those up to it are laid end to end (scan_lists), which fills every step
+// whatever their lengths but reads them to their ends, where a list by itself
+// is left at its key. Beyond a step and a half of entries the latter is worth more:
+// with the line at 2048 and at 384, the call, a clique of 2000 vertices 368 and 109 us
+// (a lane a list: 266), of 390 84 and 50, ER of 20000 vertices and 1024 entries each
+// 168 and 84; lists of about 256 are the same either way, but with the line there
+// ER of 65536 and 256, all unmatched, took 116 against 110. It also bounds the
+// laid-out length of a wavefront's 64 lists.
+constexpr int64_t kFlatList = 384;
 // A matched vertex whose list is longer than this leaves the search for its
 // edge to its mate when the mate's list is shorter.
 constexpr int64_t kOwnList = 32;
@@ -122,7 +128,7 @@ __device__ __forceinline__ void wave_sync() {
 // random reads. What describes the call (Ids) is the same for all lanes and
 // stays in scalar registers, a list is one 16-byte LDS read, the loads of a
 // step are all issued before the first is waited for, and the kernels fit 64
-// registers without spills, so two workgroups share a CU. Against a list that
+// vector registers without spilling any, so two workgroups share a CU. Against a list that
 // names its graph and generic pointers, the call: a mesh of 1e7 vertices
 // 120 -> 96 us, ER of 2^22 vertices and 16 entries each 136 -> 131, R-MAT-25 683 -> 671;
 // with two registers spilled ER took 158.

@@ -277,3 +277,27 @@ def test_batch_check_of_tiny_members_costs_as_one_graph():
     print("%.0f us for %d members, %.0f us for one graph" % (many, n, one))
     assert many < 3 * one
     b.close()
+
+
+# lists at the length where they are no longer laid end to end
+@pytest.mark.parametrize("k", [382, 383, 384, 385])
+@pytest.mark.parametrize("one_sided", [False, True])
+def test_check_longest_laid_out_lists(k, one_sided):
+    test_check_long_lists(k, one_sided)
+
+
+def test_check_leaves_a_long_list_at_its_key():
+    # a clique of 2000: matched, a list is needed up to the mate, half of it in
+    # the mean; all free, to its end. Read to the end it took 0.9 of the time,
+    # left at the mate 0.4
+    n = 2000
+    i = np.arange(n, dtype=np.int32)
+    nbr = np.broadcast_to(i, (n, n))[i[:, None] != i[None, :]]
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda") * (n - 1)
+    g = mm.Graph(off, torch.from_numpy(nbr.copy()).cuda(), symmetric=True)
+    mates, free = g.run(), torch.full((n,), -1, dtype=torch.int32, device="cuda")
+    assert g.check(mates)["ok"] and g.check(free)["uncovered"] == n * (n - 1)
+    matched, unmatched = median_us(lambda: g.check(mates)), median_us(lambda: g.check(free))
+    print("%.0f us matched, %.0f us unmatched" % (matched, unmatched))
+    assert matched < 0.7 * unmatched
+    g.close()
