@@ -29,7 +29,13 @@ namespace {
 // Counters of kGroup iterations (touched, selecting, pairs of each), read back
 // together: a wait for every iteration costs more than the iteration on a
 // graph of up to some 1e5 vertices. The iterations of a group that come after
-// the last one see that it selected nothing and end at once.
+// the last one see that it selected nothing and end at once. They still cost
+// their launches (two each, 4 to 5 us a piece), so a graph without entries, which
+// takes one iteration, gets a first group of one (a run 35 us, 114 with eight), and
+// one with at most an entry per vertex, which is mostly edges by themselves,
+// where two will do, a group of two (50 such edges 38 us and 110). Everywhere else a
+// run takes four iterations and more, and a first group of two costs a wait (ER of
+// 1000 vertices 130 us against 105).
 // With one add per workgroup and four entries per lane in flight a run takes, before
 // and after: ER-65536 559 and 331 us, R-MAT-18 1450 and 475, a mesh of 5e5 vertices
 // 1573 and 190, ER of 4e6 10.2 and 2.9 ms (of which 0.8 ms per iteration were adds).
@@ -241,9 +247,11 @@ mm_status mm_ems_run(mm_handle h, void* stream, uint64_t seed, void* scratch,
     const Grid gr = grid_of(n);
     // every iteration matches at least one pair, so n/2 + 1 iterations always suffice
     bool done = false;
-    for (int64_t it = 0; it <= n / 2 + 1 && !done; it += kGroup) {
-      HIP_TRY(hipMemsetAsync(ctr, 0, kGroup * 3 * sizeof(unsigned long long), s));
-      for (int k = 0; k < kGroup; ++k) {
+    const int64_t m = mmi::handle_m(h);
+    int group = m == 0 ? 1 : m <= n ? 2 : kGroup;
+    for (int64_t it = 0; it <= n / 2 + 1 && !done; it += group, group = kGroup) {
+      HIP_TRY(hipMemsetAsync(ctr, 0, group * 3 * sizeof(unsigned long long), s));
+      for (int k = 0; k < group; ++k) {
         unsigned long long* c = ctr + 3 * k;
         const unsigned long long* prev = k ? c - 3 : nullptr;
         if (mmi::handle_off64(h))
@@ -256,8 +264,8 @@ mm_status mm_ems_run(mm_handle h, void* stream, uint64_t seed, void* scratch,
         HIP_TRY(hipGetLastError());
       }
       unsigned long long c[kGroup * 3];
-      HIP_TRY(mmi::read_back(c, ctr, sizeof(c), s));
-      for (int k = 0; k < kGroup && !done; ++k) {
+      HIP_TRY(mmi::read_back(c, ctr, group * 3 * sizeof(unsigned long long), s));
+      for (int k = 0; k < group && !done; ++k) {
         ++iters;
         touched += (int64_t)c[3 * k];
         pairs += (int64_t)c[3 * k + 2];

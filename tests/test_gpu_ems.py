@@ -1,6 +1,8 @@
 """The mutual-selection baseline (Section II-C) on the GPU against the
 oracle's weighted greedy: with fixed edge weights both reach the greedy
 matching in descending weight order, so they must agree bit for bit."""
+import time
+
 import numpy as np
 import pytest
 
@@ -69,3 +71,97 @@ def test_ems_reads_more_than_skipper():
     assert oracle.check(g, out.cpu().numpy()).ok
     assert st["iterations"] >= 2
     assert st["touched"] > 2 * (skipper["touched"] + skipper["assist_reads"])
+
+
+def _mix(z):
+    z = z + np.uint64(0x9E3779B97F4A7C15)
+    z = (z ^ (z >> np.uint64(30))) * np.uint64(0xBF58476D1CE4E5B9)
+    z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94D049BB133111EB)
+    return z ^ (z >> np.uint64(31))
+
+
+def rounds(csr, seed):
+    """(iterations, ids read) of the mutual selection, round by round: the last
+    round finds nothing to select; a round reads the lists of free vertices."""
+    off = csr.off.astype(np.int64)
+    deg = np.diff(off)
+    x, y = np.repeat(np.arange(csr.n), deg), csr.nbr.astype(np.int64)
+    key = (np.minimum(x, y).astype(np.uint64) << np.uint64(32)) | np.maximum(x, y).astype(np.uint64)
+    with np.errstate(over="ignore"):
+        w = _mix(_mix(np.array([seed], dtype=np.uint64)) ^ key)
+    order = np.lexsort((key, ~w, x))  # each list by falling weight, then rising key
+    x, y = x[order], y[order]
+    mate = np.full(csr.n, -1)
+    iterations = touched = 0
+    while True:
+        free = mate == -1
+        iterations += 1
+        touched += int(deg[free].sum())
+        live = np.flatnonzero(free[x] & free[y] & (x != y))
+        if live.size == 0:
+            return iterations, touched
+        first = live[np.r_[True, x[live][1:] != x[live][:-1]]]
+        sel = np.full(csr.n, -1)
+        sel[x[first]] = y[first]
+        v = np.flatnonzero(sel >= 0)
+        m = v[sel[sel[v]] == v]
+        mate[m] = sel[m]
+
+
+def _clique(n, among=0):
+    return graphgen.from_edges(max(n, among), [(i, j) for i in range(n) for j in range(i + 1, n)])
+
+
+# runs of 1 to 12 iterations: the counters are read back for eight iterations at
+# a time, or (few entries) for one or two first, and a run may end before, at and
+# after such a wait
+@pytest.mark.parametrize("make,seed,iterations", [
+    (lambda: graphgen.from_edges(9, np.zeros((0, 2))), 1, 1),
+    (lambda: graphgen.from_edges(9, [(4, 4)]), 1, 1),
+    (lambda: graphgen.from_edges(10, [(i, i + 1) for i in range(9)]), 3, 2),
+    (lambda: graphgen.from_edges(500, [(2 * i, 2 * i + 1) for i in range(250)]), 1, 2),
+    (lambda: graphgen.grid(4, 4), 1, 3),
+    (lambda: graphgen.from_edges(40, [(i, i + 1) for i in range(9)]), 1, 3),
+    (lambda: graphgen.from_edges(100000, [(i, i + 1) for i in range(30000)]), 1, 5),
+    (lambda: _clique(300, 100000), 1, 9),
+    (lambda: _clique(300, 100000), 2, 10),
+    (lambda: _clique(300, 100000), 6, 11),
+    (lambda: graphgen.er(10, 8, seed=4), 1, 4),
+    (lambda: graphgen.er(300, 8, seed=4), 3, 7),
+    (lambda: graphgen.er(1000, 8, seed=4), 4, 8),
+    (lambda: _clique(400), 9, 9),
+    (lambda: graphgen.er(30000, 8, seed=4), 3, 10),
+    (lambda: _clique(400), 1, 10),
+    (lambda: _clique(400), 3, 11),
+    (lambda: _clique(400), 7, 12),
+])
+def test_ems_counts_every_iteration(make, seed, iterations):
+    csr = make()
+    want = rounds(csr, seed)
+    assert want[0] == iterations
+    h = mm.Graph(*to_dev(csr), symmetric=True)
+    mate, st = h.ems(seed=seed)
+    np.testing.assert_array_equal(mate.cpu().numpy(), oracle.greedy_weighted(csr, seed)[0])
+    assert (st["iterations"], st["touched"]) == want
+    h.close()
+
+
+def test_ems_short_run_pays_for_its_own_iterations():
+    # an edgeless graph (one iteration) against one of eight; with eight
+    # iterations launched for either it took 0.9 of the time, with its own 0.4
+    def median(csr):
+        h = mm.Graph(*to_dev(csr), symmetric=True)
+        h.ems(seed=4)
+        times = []
+        for _ in range(21):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            h.ems(seed=4)
+            times.append(time.perf_counter() - t)
+        h.close()
+        return 1e6 * sorted(times)[10]
+
+    one = median(graphgen.from_edges(1000, np.zeros((0, 2))))
+    eight = median(graphgen.er(1000, 8, seed=4))
+    print("%.0f us for one iteration, %.0f us for eight" % (one, eight))
+    assert one < 0.65 * eight
