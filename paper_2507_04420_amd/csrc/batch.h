@@ -63,7 +63,7 @@ struct BatchPlan {
   int32_t lds_words;  // LDS words of the largest of them (0: no such graph)
 };
 
-// Enqueues one pass: fills, queue reset, persistent sweep, output fix-up.
+// Enqueues one pass: fills, queue counter, persistent sweep, output fix-up.
 hipError_t enqueue_pass(const BatchPlan& bp, hipStream_t s);
 
 // Device check of a concatenated CSR (bits as for the single-graph check).

@@ -457,3 +457,59 @@ def test_creating_a_batch_does_not_sort_its_members():
     equal = create_us(np.full(G, 16))
     print("%.0f us for mixed sizes, %.0f us for equal ones" % (mixed, equal))
     assert mixed < 1.5 * equal
+
+
+# as many work items as wavefronts in flight, fewer and more: the wavefronts'
+# first items are theirs by number, the rest are popped, if there are any
+@pytest.mark.parametrize("items", [1, 2, 63, 1023, 4097, 5120, 6144, 7167, 7168, 7169, 8191, 8192, 8193, 30000])
+@pytest.mark.parametrize("tuning", [mm.Tuning(whole_graph_vertices=0, wave_vertices=64, wg_size=64),
+                                    mm.Tuning(whole_graph_vertices=0, wave_vertices=64, layout=_lib.MM_LAYOUT_U8,
+                                              lazy_init=1),
+                                    mm.Tuning(whole_graph_vertices=0, mesh_wave_vertices=64, disperse=1)])
+def test_every_work_item_is_swept_once(items, tuning):
+    # members of 64 vertices, each a perfect matching: one item each, one result
+    n = 64 * items
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda")
+    mate = (torch.arange(n, dtype=torch.int32, device="cuda") % 64) ^ 1
+    b = mm.Batch(off, mate.clone(), np.arange(items + 1) * 64, symmetric=True, tuning=tuning)
+    assert b.items == items
+    out = torch.empty(n, dtype=torch.int32, device="cuda")
+    for _ in range(3):
+        out.fill_(-5)
+        b.run(out)
+        b.sync()
+        assert torch.equal(out, mate)
+    b.close()
+    s = mm.Batch(off, mate.clone(), np.arange(items + 1) * 64, symmetric=True, tuning=tuning, stats=True)
+    s.run()
+    s.sync()
+    assert s.stats()["sources"] == n and s.stats()["pairs"] == n // 2
+    s.close()
+
+
+def test_small_blocks_are_not_bound_by_their_queue():
+    # 5000 members of one block each, no entries, against one graph of as many
+    # blocks: with every block popped, one after the other, it took 6 times as long
+    items = 5000
+    n = 64 * items
+    off = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    nbr = torch.zeros(0, dtype=torch.int32, device="cuda")
+    t = mm.Tuning(whole_graph_vertices=0, wave_vertices=64, min_waves=0)
+    out = torch.empty(n, dtype=torch.int32, device="cuda")
+
+    def median_us(h):
+        h.run(out)
+        times = []
+        for _ in range(21):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            h.run(out)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        h.close()
+        return 1e6 * sorted(times)[10]
+
+    many = median_us(mm.Batch(off, nbr, np.arange(items + 1) * 64, tuning=t))
+    one = median_us(mm.Graph(off, nbr, tuning=t))
+    print("%.0f us for %d members, %.0f us for one graph" % (many, items, one))
+    assert many < 2.5 * one
