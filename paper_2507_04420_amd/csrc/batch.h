@@ -49,6 +49,7 @@ struct BatchPlan {
   unsigned long long* stats;
   int32_t layout, protocol;
   bool hint, lazy, stats_on;
+  bool noted;  // blocks with dispersed lanes among the items (sweep.h)
   int wg_size, num_cus;
   int32_t* mate;  // base of all mate entries (N of them)
   int64_t N;

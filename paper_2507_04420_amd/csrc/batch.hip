@@ -146,7 +146,7 @@ __device__ __forceinline__ LayoutPacked<2, true> layout_of(const GraphDesc& d, i
 // more items than wavefronts) until the table is exhausted; each item is one
 // sweep_block of one graph. Every wavefront reaches the exit (the counter only
 // grows, and each item's sweep has its own trip budget).
-template <class Layout, bool HINT, bool LAZY, bool STATS>
+template <class Layout, bool HINT, bool LAZY, bool STATS, bool NOTED>
 __global__ __launch_bounds__(256) void batch_sweep_kernel(SweepParams p,
                                                          const GraphDesc* __restrict__ descs,
                                                          const WorkItem* __restrict__ items,
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void batch_sweep_kernel(SweepParams p,
                                                          uint32_t* queue,
                                                          unsigned long long* stats) {
   extern __shared__ uint4 sweep_lds[];
-  QSlot* ring = wave_ring(sweep_lds, true);
+  QSlot* ring = wave_ring(sweep_lds, NOTED);
   Counters<STATS> cnt;
   const int lane = (int)(threadIdx.x & 63);
   uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane(
@@ -184,8 +184,8 @@ __global__ __launch_bounds__(256) void batch_sweep_kernel(SweepParams p,
     if (pieces && pp.hub_wave)
       sweep_pieces_wave<Layout, HINT, STATS>(pp, d.nbr, L, w.vb, nv, cnt);
     else
-      sweep_block<int64_t, Layout, HINT, LAZY, STATS>(pp, d.off, d.nbr, L, w.vb, nv, ring,
-                                                      wave_noted(ring, noted_sources(pp)), cnt);
+      sweep_block<int64_t, Layout, HINT, LAZY, STATS, NOTED>(
+          pp, d.off, d.nbr, L, w.vb, nv, ring, wave_noted(ring, NOTED && noted_sources(pp)), cnt);
     if (!queue) break;
     if (lane == 0)
       it = __hip_atomic_fetch_add(queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -221,9 +221,11 @@ int grid_for(int64_t words) {
 
 template <class Layout, bool HINT, bool LAZY, bool STATS>
 hipError_t launch_persistent(const BatchPlan& bp, hipStream_t s) {
-  auto kern = batch_sweep_kernel<Layout, HINT, LAZY, STATS>;
+  constexpr bool kBoth = has_plain_build<Layout, LAZY, STATS>;
+  auto kern = batch_sweep_kernel<Layout, HINT, LAZY, STATS, !kBoth>;
+  if (kBoth && bp.noted) kern = batch_sweep_kernel<Layout, HINT, LAZY, STATS, true>;
   int per_cu = 0;
-  const size_t lds = (bp.wg_size / 64) * wave_lds_bytes(true);  // meshes among the graphs
+  const size_t lds = (bp.wg_size / 64) * wave_lds_bytes(!kBoth || bp.noted);
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, bp.wg_size, lds);
   if (e != hipSuccess) return e;
   if (per_cu < 1) per_cu = 1;
@@ -562,7 +564,7 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
   lds_items.resize((size_t)n_lds);
   // work items: a small graph is one item (one wavefront), a larger one an
   // item per block; a mesh's blocks are shorter, and its lanes dispersed
-  bool descs_changed = false;
+  bool descs_changed = false, meshes = false;
   for (int32_t g = 0; g < G; ++g) {
     mmb::GraphDesc& d = descs[g];
     int64_t step = lay.wave_vertices;
@@ -570,6 +572,7 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
       step = d.n;
     } else if (find_meshes && !d.not_mesh) {
       d.flags |= mmb::kMesh;
+      meshes = true;
       step = lay.mesh_wave_vertices;
       descs_changed = true;
     }
@@ -671,6 +674,7 @@ mm_status finish_create(std::vector<mmb::GraphDesc>& descs, const std::vector<in
   mmb::BatchPlan& p = b->plan;
   p.params.wave_vertices = lay.wave_vertices;
   p.params.disperse = t.disperse;
+  p.noted = t.disperse || meshes;
   p.params.assist_after = t.assist_after;
   p.params.scan_width = t.scan_width;
   p.params.stream_loads = t.stream_loads;

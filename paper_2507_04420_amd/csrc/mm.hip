@@ -275,7 +275,7 @@ __global__ void validate_kernel(const OffT* __restrict__ off, const int32_t* __r
 // chunk_count (device, or null): the number of pieces when only the device
 // knows it (the table was filled by this pass's own stream); n_chunks is then
 // the table's capacity, which sizes the grid.
-template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS>
+template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS, bool NOTED>
 __device__ __forceinline__ void sweep_graph(SweepParams p, const OffT* __restrict__ off,
                                             const int32_t* __restrict__ nbr, int64_t n,
                                             int64_t v_begin, int64_t main_waves, int64_t n_chunks,
@@ -289,7 +289,7 @@ __device__ __forceinline__ void sweep_graph(SweepParams p, const OffT* __restric
     __syncthreads();
   }
   const int64_t wave = uniform64(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const bool noted = noted_sources(p);
+  const bool noted = NOTED && noted_sources(p);
   int64_t vb, nv;
   if (wave < main_waves) {
     vb = v_begin + wave * p.wave_vertices;
@@ -321,8 +321,8 @@ __device__ __forceinline__ void sweep_graph(SweepParams p, const OffT* __restric
   extern __shared__ uint4 sweep_lds[];
   QSlot* ring = wave_ring(sweep_lds, noted);
   Counters<STATS> cnt;
-  sweep_block<OffT, Layout, HINT, LAZY, STATS>(p, off, nbr, L, vb, nv, ring, wave_noted(ring, noted),
-                                               cnt);
+  sweep_block<OffT, Layout, HINT, LAZY, STATS, NOTED>(p, off, nbr, L, vb, nv, ring,
+                                                      wave_noted(ring, noted), cnt);
   if (STATS) cnt.flush(stats);
 }
 
@@ -330,15 +330,15 @@ __device__ __forceinline__ void sweep_graph(SweepParams p, const OffT* __restric
 // dependent memory operations are the bound, so what keeps registers free is
 // worth its instructions: with the block's bounds in registers of every lane
 // instead of scalars the sweep took 81 to 88, and five fitted.
-template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS>
+template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS, bool NOTED>
 __global__ __launch_bounds__(256) void sweep_kernel(SweepParams p, const OffT* __restrict__ off,
                                                    const int32_t* __restrict__ nbr, int64_t n,
                                                    int64_t v_begin, int64_t main_waves,
                                                    int64_t n_chunks,
                                                    const unsigned long long* chunk_count, Layout L,
                                                    unsigned long long* stats) {
-  sweep_graph<OffT, Layout, HINT, LAZY, STATS>(p, off, nbr, n, v_begin, main_waves, n_chunks,
-                                               chunk_count, L, stats);
+  sweep_graph<OffT, Layout, HINT, LAZY, STATS, NOTED>(p, off, nbr, n, v_begin, main_waves, n_chunks,
+                                                      chunk_count, L, stats);
 }
 
 // A graph swept whole by one wavefront, its states in that wavefront's LDS
@@ -510,15 +510,17 @@ hipError_t launch_sweep(const mm_graph* g, const Layout& L, hipStream_t s) {
   pl.chunks = g->chunks;
   const int wpb = g->tun.wg_size / 64;
   const int64_t blocks = (waves + chunk_waves + wpb - 1) / wpb;
+  constexpr bool kBoth = has_plain_build<Layout, LAZY, STATS>;
+  auto kern = sweep_kernel<OffT, Layout, HINT, LAZY, STATS, !kBoth>;
+  if (kBoth && noted_sources(p)) kern = sweep_kernel<OffT, Layout, HINT, LAZY, STATS, true>;
   const size_t lds = wpb * wave_lds_bytes(noted_sources(p));
   if (blocks == 0) return hipSuccess;
   if (g->timing) {
     hipError_t e = hipEventRecord(g->timing->before(), s);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((sweep_kernel<OffT, Layout, HINT, LAZY, STATS>), dim3((unsigned)blocks),
-                     dim3(g->tun.wg_size), lds, s, pl, off, nbr, g->n, v_begin, waves, g->n_chunks,
-                     g->chunk_count, L, stats);
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(g->tun.wg_size), lds, s, pl, off, nbr, g->n,
+                     v_begin, waves, g->n_chunks, g->chunk_count, L, stats);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (g->timing) {

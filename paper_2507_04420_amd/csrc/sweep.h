@@ -193,6 +193,15 @@ __host__ __device__ __forceinline__ bool noted_sources(const SweepParams& p) {
   return p.disperse && !p.whole;
 }
 
+// Sweeps that keep no such bits have a build without them where a sweep is
+// timed (NOTED of sweep_block): looking for them took 0.5 to 1.5% (the er entry's sweep
+// of 4e6 vertices and 16 entries each 297 -> 293 us, of 1e6 and 200 323 -> 318,
+// the rmat entry's of R-MAT-25 828 -> 825). The others, lazy, relabelled and
+// instrumented, look for them always: a second build of each would add half
+// again to the library.
+template <class Layout, bool LAZY, bool STATS>
+constexpr bool has_plain_build = !LAZY && !STATS && !Layout::kRelabelled;
+
 // This wavefront's ring in the workgroup's dynamic LDS, and its bits, or null.
 __device__ __forceinline__ QSlot* wave_ring(void* lds, bool noted) {
   return reinterpret_cast<QSlot*>(static_cast<uint8_t*>(lds) +
@@ -229,11 +238,12 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 // its mate array and hint, all based at the graph's first vertex).
 // HINT: skip matched neighbours by the matched hint (a bit or byte per vertex) instead of the
 // state word.
-// ring: this wavefront's LDS ring of kQueue slots; done: its bits of matched
-// sources, or null (a graph swept whole, whose schedule has no such check).
+// NOTED: the wavefront may keep bits of matched sources.
+// ring: this wavefront's LDS ring of kQueue slots; done: with NOTED, its bits, or
+// null (a graph swept whole, whose schedule has no such check).
 // OffP / NbrP: the pointer types of off and nbr (generic by default; a caller
 // that knows the graph is in device memory may pass global pointers).
-template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS,
+template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS, bool NOTED,
           class OffP = const OffT*, class NbrP = const int32_t*>
 __device__ __forceinline__ void sweep_block(const SweepParams& a, OffP __restrict__ off,
                                             NbrP __restrict__ nbr, const Layout& L,
@@ -262,7 +272,7 @@ __device__ __forceinline__ void sweep_block(const SweepParams& a, OffP __restric
                      : a.chunks ? 65536 + 8 * nv * a.hub_chunk
                                 : 65536 + 8 * ((int64_t)off[vb + nv] - (int64_t)off[vb]);
 
-  if (done)
+  if (NOTED && done)
     for (int k = lane; k < kDone / 32; k += 64) done[k] = 0u;
   auto done_bit = [&](int32_t y) -> uint32_t {  // kDone: none
     const uint32_t k = (uint32_t)(y - (int32_t)vb);
@@ -270,7 +280,7 @@ __device__ __forceinline__ void sweep_block(const SweepParams& a, OffP __restric
   };
   auto is_done = [&](int32_t y) -> bool {
     const uint32_t k = done_bit(y);
-    return done && k < (uint32_t)kDone && ((done[k >> 5] >> (k & 31)) & 1u);
+    return NOTED && done && k < (uint32_t)kDone && ((done[k >> 5] >> (k & 31)) & 1u);
   };
 
   // Filter reads: the hint bit, or the vertex's own state word.
@@ -447,7 +457,7 @@ __device__ __forceinline__ void sweep_block(const SweepParams& a, OffP __restric
           else
             L.commit(u, v);
           const uint32_t k = done_bit(u == x ? v : u);
-          if (done && k < (uint32_t)kDone)
+          if (NOTED && done && k < (uint32_t)kDone)
             __hip_atomic_fetch_or(done + (k >> 5), 1u << (k & 31), __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_WAVEFRONT);
           if (STATS) {

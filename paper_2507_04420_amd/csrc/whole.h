@@ -473,7 +473,7 @@ __device__ __forceinline__ void sweep_whole_lds(SweepParams p, const OffT* __res
   lay.mate = nullptr;
   lay.hint = Hint{nullptr, 0};
   lay.mate16 = reinterpret_cast<int16_t*>(lds + words);
-  sweep_block<OffT, LayoutLds, false, false, STATS, GOff, GNbr>(p, (GOff)off, (GNbr)nbr, lay, 0, n,
+  sweep_block<OffT, LayoutLds, false, false, STATS, false, GOff, GNbr>(p, (GOff)off, (GNbr)nbr, lay, 0, n,
                                                                 q, nullptr, cnt);
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
