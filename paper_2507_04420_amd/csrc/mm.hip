@@ -494,6 +494,27 @@ hipError_t launch_whole_lds(const mm_graph* g, int32_t* mate, hipStream_t s) {
   return e;
 }
 
+// LDS per wavefront of a sweep. Its registers let seven wavefronts share a SIMD,
+// which pays where lanes wait for each other's reservations or read few states
+// (a mesh of 7000^2 1.41 ms, 2.25 with five; the tuned entries, which examine upper
+// neighbours only, up to 10%). A sweep of all neighbours in long blocks over a large
+// graph whose edges leave them is bound by the lines of states it reads again,
+// and more wavefronts only push those out of L2: it gets LDS for five, if the tuning
+// does not ask for the upper neighbours only (default
+// tuning, seven and five: ER of 2^25 vertices and 16 entries each 4.98 and 4.88 ms, of
+// 2^24 2.60 and 2.57, R-MAT-24 1.17 and 1.14, R-MAT-25 1.83 and 1.78; ER of 2^22 0.67
+// either way). Blocks of 64 and 256 are left alone: dispersed over R-MAT-24 five are
+// 4 to 20% slower.
+size_t sweep_lds_bytes(const mm_graph* g, const SweepParams& p) {
+  // 20 or 21 wavefronts in a CU's 160 KB, in workgroups of one to four, whose
+  // LDS is given out in units of 1280 bytes (16 for the slots of hub pieces)
+  constexpr size_t kFivePerSimd = 7664;
+  static_assert(sizeof(QSlot) * kQueue + kDone / 8 <= kFivePerSimd, "room for ring and bits");
+  const bool five = !g->tun.upper_only && !g->relabel && p.wave_vertices >= 1024 &&
+                    g->n >= (int64_t)1 << 23 && g->m / 4 > g->n;
+  return five ? kFivePerSimd : wave_lds_bytes(noted_sources(p));
+}
+
 template <typename OffT, class Layout, bool HINT, bool LAZY, bool STATS>
 hipError_t launch_sweep(const mm_graph* g, const Layout& L, hipStream_t s) {
   const SweepParams p = make_params(g);
@@ -513,7 +534,7 @@ hipError_t launch_sweep(const mm_graph* g, const Layout& L, hipStream_t s) {
   constexpr bool kBoth = has_plain_build<Layout, LAZY, STATS>;
   auto kern = sweep_kernel<OffT, Layout, HINT, LAZY, STATS, !kBoth>;
   if (kBoth && noted_sources(p)) kern = sweep_kernel<OffT, Layout, HINT, LAZY, STATS, true>;
-  const size_t lds = wpb * wave_lds_bytes(noted_sources(p));
+  const size_t lds = wpb * sweep_lds_bytes(g, p);
   if (blocks == 0) return hipSuccess;
   if (g->timing) {
     hipError_t e = hipEventRecord(g->timing->before(), s);
