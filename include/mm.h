@@ -166,11 +166,11 @@ typedef struct {
   int32_t hub_chunk;     /* entries per piece of a long list, >= 1 */
   int32_t whole_graph_lds; /* 1: a graph swept whole by one wavefront (see
                             whole_graph_vertices) with at most MM_LDS_WHOLE_MAX
-                            vertices keeps its states in that wavefront's LDS,
-                            since no other wavefront reads them: 2 bits per
-                            vertex, with the two-phase protocol whatever the
-                            layout and protocol fields say; the mates are
-                            written to the output as pairs are committed. Not
+                            vertices keeps its states and mates in that
+                            wavefront's LDS, since no other wavefront reads
+                            them: 16 bits per vertex, with the two-phase protocol
+                            whatever the layout and protocol fields say; the
+                            output is written once, at the end. Not
                             with relabel. 0: states in device memory, as for
                             every other graph */
   int32_t mesh_wave_vertices; /* batches: a member graph none of whose lists holds
@@ -242,10 +242,10 @@ typedef struct {
                             2: every state read takes one candidate (ids are
                             still read scan_width at a time). 0: every read
                             takes a whole step's candidates */
-  int32_t occupancy;     /* 0 or 6: no effect (kept for stored tunings). 6 chose a
-                            build of the sweep kernel limited to six wavefronts'
-                            share of a SIMD's registers; every build now fits
-                            seven */
+  int32_t occupancy;     /* 0 or 6: no effect (kept for callers and stored tunings
+                            that set it). 6 once chose a build of the sweep kernel
+                            for six wavefronts per SIMD; the registers of every
+                            build that is timed now fit seven */
   int64_t iter_cap;      /* loop-trip budget per wavefront; 0 = default of
                             65536 + 8 x (neighbour entries of its block);
                             exceeding it raises MM_ERR_NO_PROGRESS */
@@ -488,7 +488,8 @@ mm_status mm_pairs(mm_handle h, void* stream, const int32_t* match, int32_t* pai
  * | max)); the result is the greedy matching in descending weight order (ties:
  * smaller key), the same on every run. Needs a handle created with
  * MM_SYMMETRIC (on a one-sided list an edge may never be selected by both
- * ends). Synchronous: waits for `stream` after every iteration. scratch:
+ * ends). Synchronous: waits for `stream` after every eight iterations (on a graph of at
+ * most an entry per vertex first after one or two). scratch:
  * device, 256-byte aligned, mm_ems_scratch_bytes(n) bytes. match_out: device,
  * n int32. stats (host, may be null): iterations run (the last one finds
  * nothing to select), ids read over all iterations, pairs.

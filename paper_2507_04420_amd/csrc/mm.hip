@@ -326,7 +326,7 @@ __device__ __forceinline__ void sweep_graph(SweepParams p, const OffT* __restric
   if (STATS) cnt.flush(stats);
 }
 
-// Seven wavefronts per SIMD (63 to 72 registers). The lanes' chains of
+// Seven wavefronts per SIMD (62 to 68 registers; instrumented 79 to 89, five). The lanes' chains of
 // dependent memory operations are the bound, so what keeps registers free is
 // worth its instructions: with the block's bounds in registers of every lane
 // instead of scalars the sweep took 81 to 88, and five fitted.

@@ -159,3 +159,24 @@ def test_whole_in_device_memory_keeps_its_schedule(graph, tuning):
         assert hashlib.sha1(mate.tobytes()).hexdigest()[:16] == WHOLE_PINS[graph, tuning]
     h.sync()
     h.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1000, 16384])
+@pytest.mark.parametrize("dtype", [torch.int32, torch.int64])
+def test_graph_without_entries(n, dtype):
+    # nothing to sweep: every vertex unmatched, alone and between other members
+    off = torch.zeros(n + 1, dtype=dtype, device="cuda")
+    nbr = torch.zeros(0, dtype=torch.int32, device="cuda")
+    out = torch.full((n,), -5, dtype=torch.int32, device="cuda")
+    g = mm.Graph(off, nbr, symmetric=True)
+    g.run(out)
+    g.sync()
+    assert (out == -1).all()
+    g.close()
+    pair = (torch.tensor([0, 1, 2], device="cuda"), torch.tensor([1, 0], dtype=torch.int32, device="cuda"))
+    b = mm.Batch.from_list([pair, (off.long(), nbr), pair, (off.long(), nbr)], symmetric=True)
+    out = torch.full((b.N,), -5, dtype=torch.int32, device="cuda")
+    b.run(out)
+    b.sync()
+    assert out.tolist() == ([1, 0] + [-1] * n) * 2
+    b.close()
