@@ -55,7 +55,7 @@ SPACE = {
     # source while waiting for the next vertex of its row), so they move
     # together
     "upper_wait": [(0, 0), (0, 1), (1, 0), (1, 1)],
-    "min_waves": [4, 8, 16, 32, 64, 2048, 16384],
+    "min_waves": [4, 8, 16, 32, 64, 2048, 7168, 16384, 131072],
     "hub_wave": [0, 1, 2],
     "hub_chunk": [64, 256, 1024, 4096],
 }
@@ -206,25 +206,37 @@ class MultiTarget:
 
 
 class BatchTarget:
-    """A many-graph batch; objective = graphs/s of a captured pass."""
+    """Many-graph batches, each its own handle; objective = their graphs over
+    the sum of the times of a captured pass of each. Beside a batch that fills
+    the GPU whatever its blocks there should be small ones, which min_waves
+    cuts shorter."""
 
     unit = "graphs/s"
     # the copies are for single graphs; whole-graph items trade batch throughput
     # for results independent of the rest of the batch (kept by the serving loop)
     dims = [d for d in SPACE if d not in COPIES and d != "hot_degree"]
 
-    def __init__(self, mix, reps: int = 5):
+    def __init__(self, mixes, reps: int = 5):
         import torch
-        self.off = torch.from_numpy(mix.off).cuda()
-        self.nbr = torch.from_numpy(mix.nbr).cuda()
-        self.vtx = mix.vtx_off
-        self.G = mix.num_graphs
+        self.parts = [(torch.from_numpy(m.off).cuda(), torch.from_numpy(m.nbr).cuda(), m.vtx_off)
+                      for m in mixes]
+        self.G = sum(m.num_graphs for m in mixes)
         self.reps = reps
-        self.sample = "%s (%d graphs, N=%d, M=%d)" % (mix.name, mix.num_graphs, mix.n, mix.m)
+        self.sample = " + ".join("%s (%d graphs, N=%d, M=%d)" % (m.name, m.num_graphs, m.n, m.m)
+                                 for m in mixes)
 
     def measure(self, t: Tuning):
+        seconds = 0.0
+        for off, nbr, vtx in self.parts:
+            s = self._pass_seconds(t, off, nbr, vtx)
+            if s is None:
+                return None
+            seconds += s
+        return self.G / seconds
+
+    def _pass_seconds(self, t: Tuning, off, nbr, vtx):
         import torch
-        b = Batch(self.off, self.nbr, self.vtx, symmetric=True, capture=True, tuning=t)
+        b = Batch(off, nbr, vtx, symmetric=True, capture=True, tuning=t)
         out = torch.empty(b.N, dtype=torch.int32, device="cuda")
         try:
             b.run(out)
@@ -241,7 +253,7 @@ class BatchTarget:
                 times.append(a.elapsed_time(e) * 1e-3)
             if not b.check(out)["ok"]:
                 return None
-            return self.G / float(np.median(times))
+            return float(np.median(times))
         finally:
             b.close()
 
@@ -347,7 +359,7 @@ def _targets(classes, seed, rmat_scale=27, grid_side=16384):
             out[c] = lambda: MultiTarget([graphgen.er(1 << 16, 16, seed=seed),
                                           graphgen.er(1 << 22, 16, seed=seed)], copies=True)
         elif c == "batch":
-            out[c] = lambda: BatchTarget(graphgen.mixture(4096, seed=seed))
+            out[c] = lambda: BatchTarget([graphgen.mixture(k, seed=seed) for k in (4096, 256, 64)])
         else:
             raise ValueError("unknown graph class %r" % c)
     return out

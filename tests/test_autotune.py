@@ -2,6 +2,7 @@
 objective (no device), rejection of candidates that fail the check, the
 stored-JSON lookup and the degree-based graph classes."""
 import json
+import os
 
 import numpy as np
 
@@ -191,3 +192,13 @@ def test_paired_dimensions_move_together():
     assert t.upper_only == 1 and t.wait_release == 1
     assert autotune._value(t, "upper_wait") == (1, 1)
     assert autotune._value(t, "layout_protocol") == (t.layout, t.protocol)
+
+
+def test_a_search_can_reach_every_stored_entry():
+    # values set by hand after a search would be lost to the next one
+    with open(os.path.join(autotune.TUNED_DIR, "gfx950_256cu.json")) as f:
+        classes = json.load(f)["classes"]
+    for name, entry in classes.items():
+        t = Tuning(**entry["tuning"])
+        for dim, values in autotune.SPACE.items():
+            assert autotune._value(t, dim) in values, (name, dim)

@@ -17,7 +17,7 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 import paper_2507_04420_amd as mm  # noqa: E402
-from paper_2507_04420_amd import _lib  # noqa: E402
+from paper_2507_04420_amd import _lib, autotune  # noqa: E402
 
 TUNINGS = {
     "u8_cas": mm.Tuning(layout=_lib.MM_LAYOUT_U8, lazy_init=0),
@@ -513,3 +513,39 @@ def test_small_blocks_are_not_bound_by_their_queue():
     one = median_us(mm.Graph(off, nbr, tuning=t))
     print("%.0f us for %d members, %.0f us for one graph" % (many, items, one))
     assert many < 2.5 * one
+
+
+@pytest.mark.parametrize("members", [16, 64])
+def test_small_batch_with_the_stored_entry(members):
+    # too few sources for the GPU's wavefronts: the entry's min_waves cuts the
+    # members into short blocks. Every member stays a maximal matching, and the
+    # size of the whole stays within 1% (of the sequential matching's size) of
+    # what the same entry gives with the library's min_waves
+    t = autotune.tuned("batch", key="gfx950_256cu")
+    mix = graphgen.mixture(members, seed=12)
+    off, nbr = torch.from_numpy(mix.off).cuda(), torch.from_numpy(mix.nbr).cuda()
+    sizes = {}
+    for min_waves in (t.min_waves, mm.Tuning().min_waves):
+        b = mm.Batch(off, nbr, mix.vtx_off, symmetric=True,
+                     tuning=mm.Tuning(**dict(t.as_dict(), min_waves=min_waves)))
+        if min_waves == t.min_waves:
+            step = -(-(mix.n // min_waves) // 64) * 64
+            assert step < t.wave_vertices
+            meshes = [int(np.diff(mix.member(g).off).max()) <= 4 for g in range(members)]
+            n = np.diff(mix.vtx_off)
+            want = sum(-(-int(k) // (t.mesh_wave_vertices if m else step)) for k, m in zip(n, meshes))
+            assert b.items >= want  # and the pieces of long lists
+            assert b.items <= want + mix.m // t.hub_chunk
+        total = []
+        for _ in range(10):
+            mate = b.run().cpu().numpy()
+            b.sync()
+            total.append(int((mate >= 0).sum()) // 2)
+        check_members(mix, mate)
+        b.close()
+        sizes[min_waves] = np.array(total)
+    short, long = sizes[t.min_waves], sizes[mm.Tuning().min_waves]
+    sgmm = sum(oracle.sgmm(mix.member(g)).pairs for g in range(members))
+    print("%d members: sizes %d..%d in short blocks, %d..%d in long ones, sequential %d" % (
+        members, short.min(), short.max(), long.min(), long.max(), sgmm))
+    assert abs(short.mean() - long.mean()) <= 0.01 * sgmm
