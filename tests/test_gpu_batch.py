@@ -415,9 +415,9 @@ def test_small_batch_keeps_about_min_waves_wavefronts():
 
 
 def test_members_kept_in_lds_in_any_order_of_sizes():
-    # placed by size in classes of 64 vertices: sizes at the classes' ends, the
-    # smallest and the largest, empty graphs among them, rising, falling, mixed
-    sizes = [1, 2, 63, 64, 65, 128, 129, 1000, 16320, 16321, 16383, 16384]
+    # placed by size, above 256 vertices in classes of 64: sizes at the classes'
+    # ends, the smallest and the largest, empty graphs among them, in three orders
+    sizes = [1, 2, 63, 64, 65, 255, 256, 257, 320, 321, 1000, 16320, 16321, 16383, 16384]
     graphs = {n: graphgen.er(n, 6, seed=n) if n > 1 else graphgen.from_edges(1, []) for n in sizes}
 
     def dev(g):
