@@ -208,6 +208,12 @@ __global__ __launch_bounds__(64) void batch_whole_lds_kernel(SweepParams p,
   extern __shared__ uint32_t whole_st[];
   Counters<STATS> cnt;
   const GraphDesc d = descs[items[blockIdx.x].desc];
+  // one vertex has no mate: a batch of 5e5 such graphs 122 us, swept 325. (The same
+  // for any graph without entries, before the loop, made every pass 1% longer.)
+  if (!STATS && __builtin_expect(d.n == 1, 0)) {
+    if (threadIdx.x == 0) mate[d.v0] = -1;
+    return;
+  }
   sweep_whole_lds<int64_t, STATS>(p, d.off, d.nbr, d.n, mate + d.v0, whole_st, queue, cnt);
   if (STATS) cnt.flush(stats);
 }

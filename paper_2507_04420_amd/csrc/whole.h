@@ -438,12 +438,6 @@ __device__ __forceinline__ void sweep_whole_lds(SweepParams p, const OffT* __res
   using GOff = const __attribute__((address_space(1))) OffT*;
   using GNbr = const __attribute__((address_space(1))) int32_t*;
   const int64_t m = (int64_t)off[n] - (int64_t)off[0];
-  // nothing to sweep: 5e5 such graphs of one vertex 123 us, with the loop 324 (off the
-  // straight path: before the loop's code it made every pass 1.5% longer)
-  if (!STATS && __builtin_expect(m == 0, 0)) {
-    for (int64_t v = lane; v < n; v += 64) mate[v] = -1;
-    return;
-  }
   if (!STATS && m >= 0 && m <= kWholeEntries) {
     lds_u16* st = reinterpret_cast<lds_u16*>(lds);
     for (int64_t i = lane; i < whole_entry_words(n) / 4; i += 64)
